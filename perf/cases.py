@@ -1,0 +1,546 @@
+"""What is measured: the work that programs have this library do, from the
+1D static interface (launch latency) to the 3D droplet collision (memory),
+through the entry points of ``paper_1912_12059_amd``.
+
+``listed()`` gives the fixed cases, ``draw(rng)`` one more of the same ranges,
+``prepare``/``run`` what a program holds before a call and the call itself,
+``work`` what one pass cannot do without, and ``exact`` the same results in
+64 bits from plain torch.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_1912_12059_amd import closure as CL
+from paper_1912_12059_amd import nsk
+
+T_RED, EPS, BETA = 0.85, 1e-3, 1e-3
+RHO_V, RHO_L = 0.3197, 1.8071  # Maxwell densities at T = 0.85
+DEV = "cuda:0"
+RK_A = (0.0, -567301805773.0 / 1357537059087.0, -2404267990393.0 / 2016746695238.0,
+        -3550918686646.0 / 2091501179385.0, -1275806237668.0 / 842570457699.0)
+RK_B = (1432997174477.0 / 9575080441755.0, 5161836677717.0 / 13612068292357.0,
+        1720146321549.0 / 2090206949498.0, 3134564353537.0 / 4481467310338.0,
+        2277821191437.0 / 14882151754819.0)
+
+
+def _steps(dim, N, nx, ny=1, nz=1, steps=2, alpha=1000.0, kappa=1e-4, precision=0, flux=0, model=0):
+    return dict(kind="steps", dim=dim, N=N, nx=nx, ny=ny, nz=nz, steps=steps, alpha=alpha, kappa=kappa,
+                precision=precision, flux=flux, model=model)
+
+
+def listed():
+    return [
+        # the 1D static interface: a few hundred nodes, all launch and latency
+        dict(_steps(1, 3, 64, steps=20, alpha=500.0), name="slab_1d"),
+        # two droplets in 2D, the size of the 2D runs: a state that fits the caches
+        dict(_steps(2, 4, 96, 96, steps=10, alpha=500.0), name="droplets_2d"),
+        # the benchmark's 3D collision in double precision ...
+        dict(_steps(3, 4, 96, 48, 48, kappa=1e-5), name="collision_3d"),
+        # ... and in mixed precision
+        dict(_steps(3, 4, 96, 48, 48, kappa=1e-5, precision=1), name="collision_3d_mixed"),
+        # HLLC flux, another degree, no extent a multiple of anything
+        dict(_steps(3, 3, 53, 27, 25, flux=1), name="collision_3d_hllc_odd"),
+        # the original NSK equations, the reference path of model comparisons
+        dict(_steps(3, 4, 48, 24, 24, kappa=1e-5, model=1), name="nsk_original_3d"),
+        # shock capturing on: indicator, sub-cell means and the FV update of a few per cent of the elements
+        dict(kind="subcell", dim=3, N=4, nx=48, ny=24, nz=24, alpha=1000.0, kappa=1e-5, threshold=-9.0, flux=0,
+             name="subcell_rhs_3d"),
+        # a run with the learned closure, the network evaluated in every stage
+        dict(kind="closure", dim=3, N=4, nx=48, ny=24, nz=24, steps=2, alpha=200.0, kappa=1e-4, precision=0,
+             every_stage=1, name="closure_3d"),
+        # one training step of that network: loss and gradient of a minibatch, then Adam
+        dict(kind="train", batch=32768, pool=1 << 20, name="closure_training_step"),
+        # one implicit step, twenty times the explicit one
+        dict(kind="implicit", dim=3, N=4, nx=24, ny=12, nz=12, alpha=1000.0, kappa=1e-5, factor=20.0, gmres_m=40,
+             precond=1, basis_fp32=0, name="implicit_step_3d"),
+        # a parameter sweep: instances of uneven size and degree advanced together in mixed precision
+        dict(kind="batch", inst=6, ny=16, steps=2, precision=1, name="sweep_batch"),
+        # what a run asks for between its steps: the diagnostics and the next step size
+        dict(kind="diag", dim=3, N=4, nx=48, ny=24, nz=24, alpha=1000.0, kappa=1e-5, precision=0, model=0,
+             name="diagnostics_3d"),
+    ]
+
+
+def _logint(r, a, b):
+    return int(round(math.exp(r.uniform(math.log(a), math.log(b)))))
+
+
+def _sizes(r, dim, N, most):
+    """Extents of at most `most` nodes, any parity, x up to about twice as long."""
+    nodes = math.exp(r.uniform(math.log(most / 200.0), math.log(most)))
+    per = max(2.0, (nodes / (N + 1) ** dim / 2.0) ** (1.0 / dim))
+    d = [max(1, int(2 * per) + r.randint(-1, 0)), max(1, int(per) + r.randint(-1, 0)), max(1, int(per))]
+    return d[:dim] + [1] * (3 - dim)
+
+
+def draw(r):
+    k = r.choice(["steps"] * 6 + ["subcell", "closure", "train", "implicit", "batch", "diag"])
+    if k == "train":
+        return dict(kind="train", batch=_logint(r, 1000, 32768), pool=_logint(r, 50_000, 1 << 20))
+    if k == "batch":
+        return dict(kind="batch", inst=r.randint(3, 6), ny=r.randint(7, 16), steps=2 * r.randint(1, 2),
+                    precision=r.randint(0, 1))
+    if k == "implicit":
+        nx, ny, nz = _sizes(r, 3, 4, 400_000)
+        return dict(kind="implicit", dim=3, N=4, nx=nx, ny=ny, nz=nz, alpha=1000.0, kappa=1e-5,
+                    factor=r.uniform(8.0, 20.0), gmres_m=r.choice([20, 40]), precond=r.randint(0, 1), basis_fp32=0)
+    dim = r.choice([1, 2, 3, 3, 3])
+    N = r.randint(1, 5 if dim == 3 else 6) if k == "steps" else r.randint(2, 5)
+    nx, ny, nz = _sizes(r, dim, N, {1: 2000, 2: 400_000, 3: 12_000_000 if k == "steps" else 3_400_000}[dim])
+    base = dict(dim=dim, N=N, nx=nx, ny=ny, nz=nz)
+    if k == "subcell":
+        return dict(kind=k, alpha=1000.0, kappa=r.choice([1e-5, 1e-4]), threshold=r.choice([-9.0, -7.0]),
+                    flux=r.randint(0, 1), **base)
+    if k == "closure":
+        return dict(kind=k, steps=2, alpha=200.0, kappa=1e-4, precision=r.randint(0, 1),
+                    every_stage=r.randint(0, 1), **base)
+    if k == "diag":
+        m = r.randint(0, 1)
+        return dict(kind=k, alpha=1000.0, kappa=1e-5, precision=0 if m else r.randint(0, 1), model=m, **base)
+    c = _steps(dim, N, nx, ny, nz, steps=r.randint(1, 4) if dim == 3 else r.randint(1, 20),
+               alpha=r.choice([500.0, 1000.0, 2000.0]))
+    if r.random() < 0.2:
+        c.update(model=1, kappa=1e-5)
+    else:
+        c.update(precision=r.randint(0, 1), flux=r.randint(0, 1))
+    return c
+
+
+# ---- inputs -----------------------------------------------------------------
+_STREAM = None
+
+
+def _stream():
+    """The one stream a program runs its solvers on (step graphs need one of their own)."""
+    global _STREAM
+    if _STREAM is None:
+        _STREAM = torch.cuda.Stream(DEV)
+    return _STREAM
+
+
+def _nel(case):
+    return [case["nx"], case["ny"], case["nz"]][: case["dim"]]
+
+
+def _box(case):
+    """Edge lengths: elements of equal extent in every direction, y and z of length 1."""
+    n = _nel(case)
+    return [n[0] / n[-1]] + [n[d] / n[-1] for d in range(1, len(n))]
+
+
+def _state(dim, N, nel, box, seed, model=0, noise=1e-3, fast=0.12):
+    """Liquid droplets (in 1D a slab) with tanh interfaces in vapour, moving towards
+    each other, c = rho, and a little noise: U[var][elem][node] on the GPU."""
+    g = np.random.Generator(np.random.PCG64(seed))
+    xi = np.polynomial.legendre.leggauss(N + 1)[0]
+    X = []
+    for d in range(dim):
+        h = box[d] / nel[d]
+        x = torch.from_numpy((np.arange(nel[d])[:, None] + 0.5 * (xi[None, :] + 1.0)) * h).to(DEV)
+        shape = [1] * (2 * dim)
+        shape[dim - 1 - d], shape[2 * dim - 1 - d] = nel[d], N + 1
+        X.append((x.reshape(shape), box[d]))
+    rad = 0.2 * min(box) * g.uniform(0.9, 1.1)
+    width = max(0.02, 1.5 * box[0] / (nel[0] * (N + 1)))
+    prof = []
+    for s in (-1.0, 1.0):
+        dist = 0.0
+        for d, (x, L) in enumerate(X):
+            ctr = L * (0.5 + (0.17 * s if d == 0 else 0.0) + g.uniform(-0.02, 0.02))
+            y = x - ctr
+            dist = dist + (y - L * torch.round(y / L)) ** 2
+        prof.append(0.5 * (1.0 - torch.tanh((torch.sqrt(dist) - rad) / width)))
+    full = prof[0].shape
+    rho = RHO_V + (RHO_L - RHO_V) * (prof[0] + prof[1]).clamp(max=1.0)
+    t = torch.Generator(device=DEV)
+    t.manual_seed(seed)
+    rho = rho + noise * (2.0 * torch.rand(full, generator=t, device=DEV, dtype=torch.float64) - 1.0)
+    v = [fast * (prof[0] - prof[1])] + [0.2 * fast * g.uniform(0.5, 1.0) * torch.sin(2 * math.pi * X[0][0] / X[0][1])
+                                        * (prof[0] + prof[1]) for _ in range(1, dim)]
+    U = torch.stack([rho] + [rho * w for w in v] + ([] if model == 1 else [rho.clone()]))
+    nn = (N + 1) ** dim
+    return U.reshape(len(U), -1, nn).contiguous()
+
+
+def _step_size(dim, N, nel, box, alpha, kappa, model):
+    """Half the smallest of the convective, viscous and capillary or relaxation limits."""
+    n2 = 2 * N + 1
+    ih = [nel[d] / box[d] for d in range(dim)]
+    s1, s2 = sum(ih), sum(x * x for x in ih)
+    a = math.sqrt(24 * T_RED / (3.0 - 1.85) ** 2 + (0.0 if model else alpha * 1.85)) + 0.3
+    dt = min(1.0 / (n2 * a * s1), 1.0 / (n2 * n2 * (4.0 / 3.0) * EPS / 0.3 * s2))
+    if model:
+        dt = min(dt, 0.25 / (n2 * n2 * math.sqrt(kappa * 1.85) * s2))
+    else:
+        dt = min(dt, 1.0 / (n2 * n2 * kappa / BETA * s2 + alpha / (BETA * 4.656757)))
+    return 0.5 * dt
+
+
+def _dt(case):
+    return _step_size(case["dim"], case["N"], _nel(case), _box(case), case["alpha"], case["kappa"],
+                      case.get("model", 0))
+
+
+def _norm(kappa):
+    dr, rm, w0 = RHO_L - RHO_V, 0.5 * (RHO_L + RHO_V), 2.0 * math.sqrt(kappa)
+    return dict(s0=rm, k0=2.0 / dr, s1=rm, k1=2.0 / dr, k2=w0 / dr, k3=w0 * w0 / dr, g0=0.01 * dr / w0, out_m=0.5,
+                out_c=0.5)
+
+
+def _params(seed):
+    """He-uniform weights and small biases of the 4-64-64-64-2 network."""
+    g = np.random.Generator(np.random.PCG64(seed))
+    out = []
+    for name, shape in CL.LAYOUT:
+        lim = math.sqrt(6.0 / shape[1]) if name.startswith("W") else 0.1
+        out.append(g.uniform(-lim, lim, size=shape).ravel())
+    return np.concatenate(out).astype(np.float32)
+
+
+def _batch_meshes(case):
+    """Uneven boxes of degree 3, 4 and 5, as in the sweep of collisions."""
+    ny, out = case["ny"], []
+    for i in range(case["inst"]):
+        nx = ny + 4 * (i % 5)
+        out.append(dict(nel=(nx, ny, ny), N=3 + i % 3, lo=(0.0, 0.0, 0.0), hi=(nx / ny, 1.0, 1.0)))
+    return out
+
+
+def _batch_dt(case):
+    return min(_step_size(3, m["N"], m["nel"], m["hi"], 1000.0, 1e-5, 0) for m in _batch_meshes(case))
+
+
+def _samples(case, seed):
+    t = torch.Generator(device=DEV)
+    t.manual_seed(seed)
+    X = torch.randn((case["pool"], 4), generator=t, device=DEV)
+    X[:, 1] = X[:, 0] + 0.05 * X[:, 1]
+    Y = torch.stack([torch.sin(X[:, 0]) * X[:, 2], X[:, 3] * X[:, 1]], 1).contiguous()
+    idx = torch.randint(0, case["pool"], (case["batch"],), generator=t, device=DEV, dtype=torch.int32)
+    return X, Y, idx
+
+
+def prepare(case, seed):
+    k = case["kind"]
+    if k == "train":
+        X, Y, idx = _samples(case, seed)
+        net = CL.Network(params=_params(seed), device=DEV)
+        ws = torch.empty(nsk.nsk_mlp_workspace_bytes(case["batch"]), dtype=torch.uint8, device=DEV)
+        return dict(case=case, net=net, X=X, Y=Y, idx=idx, ws=ws)
+    if k == "batch":
+        meshes = _batch_meshes(case)
+        b = nsk.Batch(meshes, alpha=1000.0, beta=BETA, eps=EPS, kappa=1e-5, precision=case["precision"])
+        for i, m in enumerate(meshes):
+            b.set_state(i, _state(3, m["N"], m["nel"], m["hi"], seed + 100 * i))
+        return dict(case=case, b=b, dt=_batch_dt(case))
+    nel, box = _nel(case), _box(case)
+    kw = dict(dim=case["dim"], N=case["N"], nel=tuple(nel), hi=tuple(box) + (1.0,) * (3 - case["dim"]), T=T_RED,
+              eps=EPS, beta=BETA, alpha=case["alpha"], kappa=case["kappa"], stream=_stream())
+    U = _state(case["dim"], case["N"], nel, box, seed, case.get("model", 0))
+    if k == "closure":
+        net = CL.Network(params=_params(seed), device=DEV)
+        s = CL.closure_solver(net, _norm(case["kappa"]), every_stage=case["every_stage"], precision=case["precision"],
+                              **kw)
+    elif k == "subcell":
+        s = nsk.Solver(subcell=1, subcell_threshold=case["threshold"], flux=case["flux"], **kw)
+    elif k == "implicit":
+        s = nsk.Solver(**kw)
+    else:
+        s = nsk.Solver(precision=case["precision"], flux=case.get("flux", 0), model=case["model"], **kw)
+    s.set_state(U)
+    return dict(case=case, s=s, U=U, dt=_dt(case))
+
+
+# ---- one pass ---------------------------------------------------------------
+def run(st):
+    case = st["case"]
+    k = case["kind"]
+    if k == "train":
+        net = st["net"]
+        loss, grad = net.loss_grad(st["X"], st["Y"], st["idx"], (1.0, 1.0), st["ws"])
+        net.adam(grad, 2e-3)
+        return dict(loss=loss, grad=grad, params=net.master)
+    if k == "batch":
+        st["b"].rk_step(st["dt"], case["steps"])
+        return dict(U=st["b"].U)
+    s = st["s"]
+    if k == "subcell":
+        return dict(R=s.rhs(st["U"]))
+    if k == "diag":
+        d = s.diagnostics()
+        keys = ("e_kin", "e_total", "l2_rho_minus_c", "rho_min", "rho_max", "max_wavespeed")
+        return dict(values=np.array([d[q] for q in keys] + list(d["mass"])), dt=np.array([s.dt_estimate(0.5)]))
+    if k == "implicit":
+        s.set_state(st["U"])  # every pass solves the same equations: the same iteration counts
+        s.esdirk_step(st["dt"] * case["factor"], 1, gmres_m=case["gmres_m"], precond=case["precond"],
+                      basis_fp32=case["basis_fp32"])
+        return dict(U=s.U)
+    s.rk_step(st["dt"], case["steps"])
+    return dict(U=s.U)
+
+
+# ---- what a pass cannot do without ------------------------------------------
+def _stage_flops(dim, N, nvar):
+    """Per node: lifting and divergence contractions along the lines, fluxes and source."""
+    n = N + 1
+    return dim * (2 * n * (dim + 1) + 2 * n * nvar) + 2.0 * dim / n * (4 * n * nvar + 60) + 20 * dim + 40
+
+
+def work(case):
+    k = case["kind"]
+    if k == "train":
+        # gathered samples, parameters, moments and gradient; forward, and backward twice that
+        par = nsk.NSK_MLP_NPARAM
+        return dict(bytes=case["batch"] * 28.0 + par * 34.0, flops=6.0 * 8576 * case["batch"])
+    if k == "batch":
+        b = f = 0.0
+        for m in _batch_meshes(case):
+            nodes = math.prod(m["nel"]) * (m["N"] + 1) ** 3
+            b += 5 * case["steps"] * nodes * 8.0 * 20
+            f += 5 * case["steps"] * nodes * _stage_flops(3, m["N"], 5)
+        return dict(bytes=b, flops=f)
+    dim, N = case["dim"], case["N"]
+    nv = dim + (1 if case.get("model", 0) else 2)
+    nodes = math.prod(_nel(case)) * (N + 1) ** dim
+    per = _stage_flops(dim, N, nv)
+    if k == "diag":  # the state once for the diagnostics and once for the step size
+        return dict(bytes=2.0 * 8 * nv * nodes, flops=2 * nodes * (40.0 + 2 * (N + 1) * dim))
+    if k == "subcell":  # state in, rates out
+        return dict(bytes=16.0 * nv * nodes, flops=nodes * (per + 2 * (N + 1) * dim))
+    if k == "implicit":  # at least the state in and out of each of the five solved stages, and one Krylov vector each
+        return dict(bytes=5 * 5 * 8.0 * nv * nodes, flops=10 * nodes * per)
+    stages = 5 * case["steps"]
+    # state and register in and out of every stage (in cache for small meshes)
+    f = nodes * per * stages
+    if k == "closure":
+        f += nodes * 2 * 8576.0 * (stages if case["every_stage"] else case["steps"])
+    return dict(bytes=stages * nodes * 8.0 * 4 * nv, flops=f)
+
+
+# ---- the same in 64 bits ----------------------------------------------------
+class _DG:
+    """Right-hand sides in plain torch, U as [var, e_{dim-1}..e_0, n_{dim-1}..n_0]."""
+
+    def __init__(self, dim, N, nel, box, alpha, kappa, flux=0, model=0):
+        self.dim, self.alpha, self.kappa, self.flux, self.model = dim, alpha, kappa, flux, model
+        self.nel, self.n = nel, N + 1
+        x, w = np.polynomial.legendre.leggauss(N + 1)
+        b = np.array([1.0 / np.prod([x[j] - x[m] for m in range(N + 1) if m != j]) for j in range(N + 1)])
+        D = np.array([[b[j] / b[i] / (x[i] - x[j]) if i != j else 0.0 for j in range(N + 1)] for i in range(N + 1)])
+        D -= np.diag(D.sum(1))
+        end = lambda s: b / (s - x) / np.sum(b / (s - x))  # noqa: E731
+        t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)  # noqa: E731
+        self.D, self.Dh, self.w = t(D), t(D.T * w[None, :] / w[:, None]), w
+        self.Lm, self.Lp = t(end(-1.0)), t(end(1.0))
+        self.cm, self.cp = t(end(-1.0) / w), t(end(1.0) / w)
+        self.h2 = [2.0 * nel[d] / box[d] for d in range(dim)]
+
+    def shape(self, nv):
+        return [nv] + [self.nel[d] for d in reversed(range(self.dim))] + [self.n] * self.dim
+
+    def ax(self, d):
+        return 2 * self.dim - d
+
+    def line(self, A, x, d):
+        return (x.movedim(self.ax(d), -1) @ A.T).movedim(-1, self.ax(d))
+
+    def trace(self, x, L, d):
+        return (x.movedim(self.ax(d), -1) * L).sum(-1)
+
+    def nxt(self, x, d):  # face values of the element after
+        return torch.roll(x, -1, self.dim - d)
+
+    def prv(self, x, d):
+        return torch.roll(x, 1, self.dim - d)
+
+    def spread(self, right, left, d):
+        """(L+ right - L- left) / w at the nodes of direction d."""
+        return (right.unsqueeze(-1) * self.cp - left.unsqueeze(-1) * self.cm).movedim(-1, self.ax(d))
+
+    def lift(self, W, d):
+        s = 0.5 * (self.trace(W, self.Lp, d) + self.nxt(self.trace(W, self.Lm, d), d))
+        return self.h2[d] * (self.spread(s, self.prv(s, d), d) - self.line(self.Dh, W, d))
+
+    def pressure(self, rho):
+        al = 0.0 if self.model else self.alpha
+        return 8 * T_RED * rho / (3 - rho) - 3 * rho**2 + 0.5 * al * rho**2
+
+    def conv(self, u, d):
+        v = u[1 + d] / u[0]
+        F = torch.zeros_like(u)
+        F[0] = u[1 + d]
+        for j in range(self.dim):
+            F[1 + j] = v * u[1 + j]
+        F[1 + d] += self.pressure(u[0])
+        return F
+
+    def sound2(self, rho):
+        return 24 * T_RED / (3 - rho) ** 2 - 6 * rho + (0.0 if self.model else self.alpha * rho)
+
+    def numflux(self, a, b, d, lam):
+        Fa, Fb = self.conv(a, d), self.conv(b, d)
+        if self.model:
+            return 0.5 * (Fa + Fb) - 0.5 * lam * (b - a)
+        ca, cb, va, vb = self.sound2(a[0]).sqrt(), self.sound2(b[0]).sqrt(), a[1 + d] / a[0], b[1 + d] / b[0]
+        if self.flux == 0:
+            return 0.5 * (Fa + Fb) - 0.5 * torch.maximum(va.abs() + ca, vb.abs() + cb) * (b - a)
+        SL, SR = torch.minimum(va - ca, vb - cb), torch.maximum(va + ca, vb + cb)
+        F = (SR * Fa - SL * Fb + SL * SR * (b - a)) / (SR - SL)
+        F[-1] = SL * SR * (b[-1] - a[-1]) / (SR - SL)
+        up = (F[0] / ((SR * b[0] - SL * a[0] - (Fb[0] - Fa[0])) / (SR - SL))) >= 0
+        for j in range(self.dim):
+            if j != d:
+                F[1 + j] = F[0] * torch.where(up, a[1 + j] / a[0], b[1 + j] / b[0])
+        return torch.where(SL >= 0, Fa, torch.where(SR <= 0, Fb, F))
+
+    def rhs(self, U, source=None):
+        n = self.dim
+        W = torch.cat([U[1 : 1 + n] / U[0], (U[:1] if self.model else U[-1:])])
+        q = [self.lift(W, d) for d in range(n)]
+        div = sum(q[d][d] for d in range(n))
+        Fv = [torch.zeros_like(U) for _ in range(n)]
+        for d in range(n):
+            for j in range(n):
+                Fv[d][1 + j] = EPS * (q[d][j] + q[j][d])
+            Fv[d][1 + d] -= EPS * 2.0 / 3.0 * div
+        lam = None
+        if self.model:
+            g = torch.stack([q[d][n] for d in range(n)])
+            lap = sum(self.lift(g[d : d + 1], d)[0] for d in range(n))
+            iso = self.kappa * (U[0] * lap + 0.5 * (g * g).sum(0))
+            for d in range(n):
+                Fv[d][1 + d] += iso
+                for j in range(n):
+                    Fv[d][1 + j] -= self.kappa * g[d] * g[j]
+            lam = ((U[1 : 1 + n] / U[0]).abs().amax(0) + self.sound2(U[0]).clamp(min=0).sqrt()).max()
+        else:
+            for d in range(n):
+                Fv[d][-1] = self.kappa / BETA * q[d][n]
+        R = torch.zeros_like(U)
+        for d in range(n):
+            up = self.nxt(self.trace(U, self.Lm, d), d)
+            s = self.numflux(self.trace(U, self.Lp, d), up, d, lam)
+            s -= 0.5 * (self.trace(Fv[d], self.Lp, d) + self.nxt(self.trace(Fv[d], self.Lm, d), d))
+            R += self.h2[d] * (self.line(self.Dh, self.conv(U, d) - Fv[d], d) - self.spread(s, self.prv(s, d), d))
+        if not self.model:
+            for d in range(n):
+                R[1 + d] += self.alpha * U[0] * q[d][n]
+            R[-1] += self.alpha / BETA * (U[0] - U[-1])
+        return R if source is None else R + source
+
+    def closure(self, U, P, nm):
+        n = self.dim
+        g = [self.h2[d] * self.line(self.D, U[:1], d)[0] for d in range(n)]
+        lap = sum(self.h2[d] * self.line(self.D, g[d].unsqueeze(0), d)[0] for d in range(n))
+        gg = sum(x * x for x in g)
+        x = torch.stack([(U[0] - nm["s0"]) * nm["k0"], (U[-1] - nm["s1"]) * nm["k1"], gg.sqrt() * nm["k2"],
+                         lap * nm["k3"]], -1).reshape(-1, 4)
+        y = torch.cat([_mlp(P, c)[-1] for c in x.split(1 << 20)]).reshape(*U.shape[1:], 2)
+        S, inv = torch.zeros_like(U), torch.rsqrt(gg + nm["g0"] ** 2)
+        for d in range(n):
+            S[1 + d] = nm["out_m"] * y[..., 0] * g[d] * inv
+        S[-1] = nm["out_c"] * y[..., 1]
+        return S
+
+    def run(self, U, dt, steps, source=None, every=True):
+        du, S = torch.zeros_like(U), None
+        for _ in range(steps):
+            for s in range(5):
+                if source is not None and (every or s == 0):
+                    S = source(U)
+                du = RK_A[s] * du + dt * self.rhs(U, S)
+                U = U + RK_B[s] * du
+        return U
+
+
+def _bf16(x):
+    return x.to(torch.float32).to(torch.bfloat16).to(torch.float64)
+
+
+def _unpack(p):
+    out, o = {}, 0
+    for name, shape in CL.LAYOUT:
+        k = math.prod(shape)
+        out[name] = p[o : o + k].reshape(shape)
+        o += k
+    return out
+
+
+def _mlp(P, x):
+    """(z1, h1, z2, h2, z3, h3, y): BF16 parameters and BF16 activations into the 64-wide products."""
+    z1 = x @ P["W1"].T + P["b1"]
+    h1 = _bf16(z1.clamp(min=0))
+    z2 = h1 @ P["W2"].T + P["b2"]
+    h2 = _bf16(z2.clamp(min=0))
+    z3 = h2 @ P["W3"].T + P["b3"]
+    h3 = z3.clamp(min=0)
+    return z1, h1, z2, h2, z3, h3, h3 @ P["W4"].T + P["b4"]
+
+
+def _exact_train(case, seed):
+    X, Y, idx = _samples(case, seed)
+    p = torch.from_numpy(_params(seed)).to(DEV)
+    P = _unpack(_bf16(p))
+    x, y = X[idx.long()].double(), Y[idx.long()].double()
+    z1, h1, z2, h2, z3, h3, out = _mlp(P, x)
+    r = out - y
+    n = case["batch"]
+    loss = 0.5 * (r * r).sum() / n
+    dy = r / n
+    d3 = (dy @ P["W4"]) * (z3 > 0)
+    d2 = (d3 @ P["W3"]) * (z2 > 0)
+    d1 = (d2 @ P["W2"]) * (z1 > 0)
+    grad = torch.cat([t.reshape(-1) for t in (d1.T @ x, d1.sum(0), d2.T @ h1, d2.sum(0), d3.T @ h2, d3.sum(0),
+                                              dy.T @ h3, dy.sum(0))])
+    new = p.double() - 2e-3 * grad / (grad.abs() + 1e-8)  # the first Adam step
+    return dict(loss=loss.reshape(1), grad=grad, params=new)
+
+
+def exact(case, seed):
+    k = case["kind"]
+    if k == "train":
+        return _exact_train(case, seed)
+    if k == "batch":
+        parts, dt = [], _batch_dt(case)
+        for i, m in enumerate(_batch_meshes(case)):
+            g = _DG(3, m["N"], m["nel"], m["hi"], 1000.0, 1e-5)
+            U = _state(3, m["N"], m["nel"], m["hi"], seed + 100 * i).reshape(g.shape(5))
+            u = g.run(U, dt, case["steps"]).reshape(-1)
+            parts.append(torch.nn.functional.pad(u, (0, -u.numel() % 32)))  # slices start at 256 bytes
+        return dict(U=torch.cat(parts))
+    if k in ("subcell", "implicit"):
+        return None
+    dim, nel, box, model = case["dim"], _nel(case), _box(case), case.get("model", 0)
+    g = _DG(dim, case["N"], nel, box, case["alpha"], case["kappa"], case.get("flux", 0), model)
+    U = _state(dim, case["N"], nel, box, seed, model)
+    flat = U.reshape(-1).shape
+    U = U.reshape(g.shape(len(U)))
+    if k == "diag":
+        return dict(values=_exact_diag(case, g, U), dt=None)
+    src = None
+    if k == "closure":
+        P = _unpack(_bf16(torch.from_numpy(_params(seed)).to(DEV)))
+        src = lambda u: g.closure(u, P, _norm(case["kappa"]))  # noqa: E731
+    return dict(U=g.run(U, _dt(case), case["steps"], src, bool(case.get("every_stage", 1))).reshape(flat))
+
+
+def _exact_diag(case, g, U):
+    n, rho = g.dim, U[0]
+    w = torch.ones((), dtype=torch.float64, device=DEV)
+    for d in range(n):
+        s = [1] * n
+        s[n - 1 - d] = g.n
+        w = w * torch.from_numpy(g.w).to(DEV).reshape(s) / g.h2[d]
+    c = rho if g.model else U[-1]
+    ek = 0.5 * (U[1 : 1 + n] ** 2).sum(0) / rho
+    gc2 = sum(g.lift(c.unsqueeze(0), d)[0] ** 2 for d in range(n))
+    W = rho * 8.0 / 3.0 * T_RED * torch.log(3 * rho / (3 - rho)) - 3 * rho * rho
+    e = ek + W + 0.5 * case["alpha"] * (rho - c) ** 2 * (0 if g.model else 1) + 0.5 * case["kappa"] * gc2
+    a = g.sound2(rho).clamp(min=0).sqrt()
+    lam = max(float(((U[1 + d] / rho).abs() + a).max()) for d in range(n))
+    vals = [(w * ek).sum(), (w * e).sum(), (w * (rho - c) ** 2).sum().sqrt(), rho.min(), rho.max()]
+    return np.array([float(v) for v in vals] + [lam] + [float((w * U[v]).sum()) for v in range(len(U))])
