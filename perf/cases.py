@@ -46,7 +46,7 @@ def listed():
         dict(_steps(3, 3, 53, 27, 25, flux=1), name="collision_3d_hllc_odd"),
         # the original NSK equations, the reference path of model comparisons
         dict(_steps(3, 4, 48, 24, 24, kappa=1e-5, model=1), name="nsk_original_3d"),
-        # shock capturing on: indicator, sub-cell means and the FV update of a few per cent of the elements
+        # shock capturing on: indicator, sub-cell means and the FV update of a tenth of the elements
         dict(kind="subcell", dim=3, N=4, nx=48, ny=24, nz=24, alpha=1000.0, kappa=1e-5, threshold=-9.0, flux=0,
              name="subcell_rhs_3d"),
         # a run with the learned closure, the network evaluated in every stage
@@ -132,9 +132,10 @@ def _box(case):
     return [n[0] / n[-1]] + [n[d] / n[-1] for d in range(1, len(n))]
 
 
-def _state(dim, N, nel, box, seed, model=0, noise=1e-3, fast=0.12):
+def _state(dim, N, nel, box, seed, model=0, fast=0.12):
     """Liquid droplets (in 1D a slab) with tanh interfaces in vapour, moving towards
-    each other, c = rho, and a little noise: U[var][elem][node] on the GPU."""
+    each other, c = rho, in 1D and 2D with a little noise: U[var][elem][node] on the GPU."""
+    noise = 1e-3 if dim < 3 else 0.0
     g = np.random.Generator(np.random.PCG64(seed))
     xi = np.polynomial.legendre.leggauss(N + 1)[0]
     X = []
