@@ -10,6 +10,7 @@ LIB = os.path.join(HERE, "libnsk.so")
 SOURCES = [os.path.join(HERE, "csrc", n) for n in ("nsk.hip", "batch.hip", "closure.hip", "implicit.hip")]
 DEPENDS = SOURCES + [
     os.path.join(HERE, "csrc", "dg_kernels.hpp"),
+    os.path.join(HERE, "csrc", "dg_1d.hpp"),
     os.path.join(HERE, "csrc", "closure.hpp"),
     os.path.join(HERE, "csrc", "host_common.hpp"),
     os.path.join(HERE, "csrc", "subcell.hpp"),

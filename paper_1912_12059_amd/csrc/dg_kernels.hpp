@@ -11,12 +11,10 @@
 //                 pointwise source, then either R (dU/dt) or the fused
 //                 low-storage Runge-Kutta stage update of U and the register.
 //
-// Work layout.  A workgroup owns EPB elements, one thread per (element, node).
-// Direction by direction, the two neighbour elements across the d-faces are
-// loaded whole with coalesced loads (one thread per node) into LDS: with
-// Gauss-Legendre nodes the element ends are not nodes, so a face trace needs
-// every node of the neighbour's line.  Face traces, the numerical flux and
-// the contraction with the derivative matrix then work from LDS.  Each face
+// Work layout.  A workgroup owns EPB elements; its threads take node pairs and
+// element lines in turn (see "Work of one workgroup" below; 1D has its own
+// layout, dg_1d.hpp).  With Gauss-Legendre nodes the element ends are not
+// nodes, so a face trace needs every node of the neighbour's line.  Each face
 // value is computed identically by both elements sharing it (same operands,
 // same order), so the scheme stays conservative bit for bit.
 //
@@ -40,7 +38,8 @@ struct ipow { static constexpr int v = B * ipow<B, E - 1>::v; };
 template <int B>
 struct ipow<B, 0> { static constexpr int v = 1; };
 
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
+__host__ __device__ constexpr int cmax(int a, int b) { return a > b ? a : b; }
+__host__ __device__ constexpr int cmin(int a, int b) { return a < b ? a : b; }
 
 // f(std::integral_constant<int, 0>), ..., f(std::integral_constant<int, K-1>)
 template <int K, int I = 0, typename F>
@@ -62,12 +61,6 @@ struct Shape {
   static constexpr int NG = NTAU + DIM;                // tau + grad c
 };
 
-template <int DIM, int NP, int EPB>
-struct Tile {
-  using Sh = Shape<DIM, NP>;
-  static constexpr int THREADS = round64(cmax(EPB * Sh::NN, EPB * 2 * Sh::NF));
-};
-
 // stride of Gauss index along direction d inside an element
 template <int NP>
 __host__ __device__ constexpr int dstride(int d) { return d == 0 ? 1 : (d == 1 ? NP : NP * NP); }
@@ -83,10 +76,19 @@ __host__ __device__ constexpr int tau_index(int i, int j) {
 }
 
 // Constants of the 1D basis and the geometry, passed by value.
+template <typename R>
+struct BasisOf {
+  R Dhat[kMaxNP][kMaxNP];  // weak-form derivative operator
+  R Lm[kMaxNP], Lp[kMaxNP];  // Lagrange polynomials at xi = -1, +1
+  R invw[kMaxNP];          // 1 / Gauss weight
+  R wp[kMaxNP], wm[kMaxNP];  // Lp / weight, Lm / weight
+};
+
 struct BasisArgs {
-  double Dhat[kMaxNP][kMaxNP];  // weak-form derivative operator
-  double Lm[kMaxNP], Lp[kMaxNP];  // Lagrange polynomials at xi = -1, +1
-  double invw[kMaxNP];          // 1 / Gauss weight
+  BasisOf<double> d;
+  BasisOf<float> f;        // the same rounded to FP32
+  __host__ __device__ const BasisOf<double>& of(double) const { return d; }
+  __host__ __device__ const BasisOf<float>& of(float) const { return f; }
 };
 
 struct MeshArgs {
@@ -175,43 +177,6 @@ __device__ __forceinline__ int remap_block(int b, int G, int nx) {
   return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
-// Per-workgroup element data: element ids (-1 past the end), neighbour ids
-// and 2/h.
-template <int DIM, int EPB>
-struct ElemInfo {
-  int e[EPB];
-  int nb[EPB][DIM][2];
-  double h2[EPB][DIM];
-};
-
-template <int DIM, int EPB>
-__device__ __forceinline__ void elem_info(ElemInfo<DIM, EPB>& info, const MeshArgs& m, int L, int tid) {
-  if (tid < EPB) {
-    const int pos = L * EPB + tid;
-    const int e = pos < m.E ? m.order[pos] : -1;
-    info.e[tid] = e;
-    if (e >= 0) {
-      int idx[3];
-      idx[0] = e % m.nel[0];
-      const int r = e / m.nel[0];
-      idx[1] = DIM > 1 ? r % m.nel[1] : 0;
-      idx[2] = DIM > 2 ? r / m.nel[1] : 0;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        info.h2[tid][d] = m.h2[d][idx[d]];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          int j[3] = {idx[0], idx[1], idx[2]};
-          j[d] = j[d] + (s ? 1 : -1);
-          if (j[d] < 0) j[d] += m.nel[d];
-          if (j[d] >= m.nel[d]) j[d] -= m.nel[d];
-          info.nb[tid][d][s] = j[0] + m.nel[0] * (j[1] + m.nel[1] * j[2]);
-        }
-      }
-    }
-  }
-}
-
 // node with Gauss index 0 along d on the line of face node f
 template <int NP>
 __device__ __forceinline__ int face_base(int d, int f) {
@@ -267,158 +232,398 @@ __device__ __forceinline__ void block_max_store(double v, double* red, double* o
 }
 
 // -------------------------------------------------------------------------
+// Work of one workgroup (2D and 3D).  A workgroup owns EPB elements in two roles:
+//   node role: a thread per pair of neighbouring nodes of an element: loads
+//     the pair's values, puts them into LDS, and at the end combines the
+//     directions' contributions and writes the pair's results;
+//   line role: the waves are given to the directions in turn, and a lane
+//     takes one (element, d-line): it forms the traces of the two neighbours'
+//     d-lines, the face values of both ends of its line and the line's
+//     contraction with the derivative matrix, all in registers (the matrix is
+//     uniform, in scalar registers), and leaves NP values per component in LDS.
+// All directions run at once, so a stage is three phases with two or three
+// barriers, where one direction after the other takes seven; a contraction
+// reads each value from LDS once instead of NP times; and only the element's
+// own values stay in LDS, 16 a node in 3D instead of the 40 of staging whole
+// neighbours beside them.  In 3D three waves serve two elements at N = 4.
+// What bounds the 3D kernels at N = 4 now is the neighbours: without their loads
+// the right-hand side runs at the rate of its streams (1.42 ms for 6.6 GB).
+//
+// Measured, ms a launch, one direction after the other / this form:
+//   3D N = 4, 96x48x48, FP64    lift 1.19 / 1.11   rhs 2.55 / 2.05
+//   3D N = 4, 96x48x48, mixed   lift 0.85 / 0.78   rhs 1.82 / 1.75
+//   a stage: 3D N = 2, 96x48x48, FP64 1.17 / 0.70; N = 5, 48x24x24, mixed 0.83 / 0.57;
+//   2D N = 4, 96x96, FP64 0.0376 / 0.0244
+// -------------------------------------------------------------------------
+// LDS position of node n of an element: even for even n, so that a pair of
+// values is one 16-byte access; the planes of lines of 2 or 4 nodes are padded
+// by two, so that the lanes of a wave reading lines of any direction meet at
+// most two to a bank.
+template <int NP>
+__host__ __device__ constexpr int lds_slot(int n) { return NP == 2 || NP == 4 ? n + 2 * (n / (NP * NP)) : n; }
+
+// Distance in LDS between neighbouring nodes of a d-line.
+template <int NP>
+__device__ __forceinline__ constexpr int lds_step(int d) {
+  return d == 2 && (NP == 2 || NP == 4) ? NP * NP + 2 : dstride<NP>(d);
+}
+
+template <int DIM, int NP, int EPB>
+struct Tile {
+  using Sh = Shape<DIM, NP>;
+  static constexpr int EPW = cmin(EPB, 64 / Sh::NF);       // elements of one wave in the line role
+  static constexpr int WPD = (EPB + EPW - 1) / EPW;        // waves per direction in the line role
+  static constexpr int NPC = (Sh::NN + 1) / 2;             // node pairs per element
+  static constexpr int THREADS = cmax(round64(EPB * NPC), 64 * DIM * WPD);
+  static constexpr int RPC = (EPW * NPC + 63) / 64;        // rounds in which a wave takes its elements' pairs
+  // LDS values per element and component: even, and off the bank period
+  static constexpr int PN = (lds_slot<NP>(Sh::NN - 1) + 2) / 2 * 2 +
+                            (NP == 2 || NP == 3 || (DIM == 2 && (NP == 4 || NP == 5)) ? 2 : 0);
+  static constexpr int SL = EPB * PN;
+};
+
+// In 1D a thread per node and one per face (dg_1d.hpp).
+template <int NP, int EPB>
+struct Tile<1, NP, EPB> {
+  static constexpr int THREADS = round64(EPB * NP);
+};
+
+// Two neighbouring values of one component, 16 bytes a lane in FP64: the unit
+// of whole-element loads and stores (the L1 takes 20 cycles for the 125
+// values of an element this way, 35 with one value a lane).
+template <typename T>
+struct __attribute__((packed, aligned(sizeof(T)))) Pair {
+  T a, b;
+};
+
+// Pair p of an element's NN values.  The last pair of an odd number holds
+// the last value alone (in both places: it is loaded one value early).
+template <int NN>
+__host__ __device__ constexpr bool pair_solo(int p) { return NN % 2 != 0 && p == NN / 2; }
+template <int NN, typename T>
+__device__ __forceinline__ Pair<T> load_pair(const T* elem, int p) {
+  const bool solo = pair_solo<NN>(p);
+  Pair<T> x = *reinterpret_cast<const Pair<T>*>(elem + 2 * p - (solo ? 1 : 0));
+  if (solo) x.a = x.b;
+  return x;
+}
+template <int NN, typename T>
+__device__ __forceinline__ void store_pair(T* elem, int p, T a, T b) {
+  if (pair_solo<NN>(p))
+    elem[2 * p] = a;
+  else
+    *reinterpret_cast<Pair<T>*>(elem + 2 * p) = Pair<T>{a, b};
+}
+
+// The same in LDS (even positions; the second value of a lone last one
+// falls into the padding).
+template <typename R>
+struct alignas(2 * sizeof(R)) LdsPair {
+  R a, b;
+};
+template <typename R>
+__device__ __forceinline__ void lds_put(R* p, R a, R b) {
+  *reinterpret_cast<LdsPair<R>*>(p) = LdsPair<R>{a, b};
+}
+template <typename R>
+__device__ __forceinline__ LdsPair<R> lds_get(const R* p) {
+  return *reinterpret_cast<const LdsPair<R>*>(p);
+}
+
+// Node role of a thread: element slot el of the workgroup and pair p of its
+// nodes, at sl in LDS.
+template <int DIM, int NP, int EPB>
+struct NodeRole {
+  using Tl = Tile<DIM, NP, EPB>;
+  int el, p, sl;
+  __device__ __forceinline__ explicit NodeRole(int tid) {
+    el = tid / Tl::NPC;
+    p = tid - el * Tl::NPC;
+    sl = el * Tl::PN + lds_slot<NP>(2 * p);
+  }
+};
+
+// LDS written by some lanes of a wave and read by others: the LDS operations
+// of one wave execute in order, so only the compiler has to keep the order.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// x, but unknown to the compiler: what is computed from it is not kept from
+// an earlier use of x
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// coordinate of element e along d
+template <int d>
+__device__ __forceinline__ int elem_coord(const MeshArgs& m, int e) {
+  const unsigned n0 = unsigned(m.nel[0]);
+  if constexpr (d == 0) return int(unsigned(e) % n0);
+  const unsigned q = unsigned(e) / n0;
+  if constexpr (d == 1) return int(q % unsigned(m.nel[1]));
+  return int(q / unsigned(m.nel[1]));
+}
+
+// Line role of a thread: the waves are given to the directions in turn, a
+// lane takes one d-line: element slot el, element e (-1: none), its two
+// d-neighbours, face node f, the line's first node and 2/h.
+struct LineRole {
+  int el = 0, e = -1, f = 0, base = 0;
+  int nb[2] = {0, 0};
+  double h2 = 0.0;
+};
+
+template <int DIM, int NP, int EPB, int d>
+__device__ __forceinline__ LineRole line_role(const MeshArgs& m, int L, int sub, int lane,
+                                              const int* __restrict__ skip) {
+  using Tl = Tile<DIM, NP, EPB>;
+  constexpr int NF = Shape<DIM, NP>::NF;
+  LineRole r;
+  const int k = lane / NF;
+  r.f = lane - k * NF;
+  r.el = sub * Tl::EPW + k;
+  const int pos = L * EPB + r.el;
+  if (k >= Tl::EPW || r.el >= EPB || pos >= m.E) return r;
+  const int e = m.order[pos];
+  if (skip && skip[e]) return r;
+  r.e = e;
+  const int c = elem_coord<d>(m, e);
+  const int step = d == 0 ? 1 : (d == 1 ? m.nel[0] : m.nel[0] * m.nel[1]);
+  r.nb[0] = c == 0 ? e + (m.nel[d] - 1) * step : e - step;
+  r.nb[1] = c == m.nel[d] - 1 ? e - (m.nel[d] - 1) * step : e + step;
+  r.base = face_base<NP>(d, r.f);
+  r.h2 = m.h2[d][c];
+  return r;
+}
+
+// How a wave gets its neighbours' lines.  Mostly its lanes read them straight
+// from memory.  A line's values along x and y lie apart, which costs the L1 44
+// cycles an element and component instead of the 20 of whole elements read a
+// pair a lane; staging whole neighbours through LDS for that (into rows that
+// the own values take afterwards) needs one more barrier and twice the LDS
+// traffic.  It wins where the lines are long and LDS values are four bytes: 3D
+// mixed precision, 0.77 against 0.79 ms a stage at N = 4 (64x32x32 elements) and
+// 0.57 against 0.62 at N = 5 (48x24x24); it loses at N = 3 (0.79 both), N = 2 (0.63
+// against 0.60) and in FP64 (N = 4 1.03 against 0.95, N = 2 0.83 against 0.70).
+template <int DIM, int NP, typename R>
+constexpr bool kStageNb = DIM == 3 && NP >= 5 && sizeof(R) == 4;
+
+// Places of a wave's neighbour pairs, round by round: the pair p and its
+// position at in LDS (-1: none), and the two neighbours.
+template <int DIM, int NP, int EPB>
+struct NbPairs {
+  using Tl = Tile<DIM, NP, EPB>;
+  int p[Tl::RPC], at[Tl::RPC];
+  int nb[2][Tl::RPC];
+  __device__ __forceinline__ NbPairs(const LineRole& ln, int sub, int lane, int (*sNb)[2]) {
+    constexpr int NF = Shape<DIM, NP>::NF;
+    if (lane < NF * Tl::EPW && ln.f == 0 && ln.el < EPB) {
+      sNb[ln.el][0] = ln.e >= 0 ? ln.nb[0] : -1;
+      sNb[ln.el][1] = ln.nb[1];
+    }
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < Tl::RPC; ++r) {
+      const int pc = lane + 64 * r, k = pc / Tl::NPC, pe = sub * Tl::EPW + k;
+      p[r] = pc - k * Tl::NPC;
+      nb[0][r] = sNb[cmin(pe, EPB - 1)][0];
+      nb[1][r] = sNb[cmin(pe, EPB - 1)][1];
+      at[r] = k < Tl::EPW && pe < EPB && nb[0][r] >= 0 ? pe * Tl::PN + lds_slot<NP>(2 * p[r]) : -1;
+    }
+  }
+};
+
+// x[v][l] = p[v * S + l * ST]: NVAL lines of a d-neighbour
+template <int NVAL, int NP, int ST, typename T>
+__device__ __forceinline__ void load_lines(const T* __restrict__ p, long long S, T (&x)[NVAL][NP]) {
+#pragma unroll
+  for (int v = 0; v < NVAL; ++v)
+#pragma unroll
+    for (int l = 0; l < NP; ++l) x[v][l] = p[v * S + l * ST];
+}
+
+// -------------------------------------------------------------------------
 // Lifting: G = (tau, grad s) from the BR1 gradients of (v, s), s = c for
 // model II (MODEL 0) and s = rho for the original NSK path (MODEL 1):
 //   q_d,i = (2/h_d) [ (L+_i w*_+ - L-_i w*_-) / omega_i - sum_l Dhat_il w_l ]
 // along each d-line, w* = (w_left + w_right) / 2 on the faces.
 // -------------------------------------------------------------------------
-template <int DIM, int NP, int EPB, typename R, typename GT, int MODEL = 0>
-__device__ __forceinline__ void lift_block(int L, int tid, const double* __restrict__ U, GT* __restrict__ G,
-                                           const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph,
-                                           double* __restrict__ lfpart = nullptr) {
+template <int DIM, int NP, int EPB, typename R, typename GT, int MODEL>
+__device__ __forceinline__ void lift_block_lines(int L, int tid, const double* __restrict__ U, GT* __restrict__ G,
+                                                 const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph,
+                                                 double* __restrict__ lfpart) {
   using Sh = Shape<DIM, NP>;
-  constexpr int NN = Sh::NN, NF = Sh::NF, NL = Sh::NLIFT;
+  using Tl = Tile<DIM, NP, EPB>;
+  constexpr int NN = Sh::NN, NL = Sh::NLIFT, SL = Tl::SL, PN = Tl::PN;
   constexpr int NV = MODEL == 1 ? DIM + 1 : DIM + 2;  // conserved variables
   constexpr int SI = MODEL == 1 ? 0 : DIM + 1;        // the lifted scalar: rho or c
-  __shared__ R sW[EPB][NL][NN];             // nodal primitives (v, s)
-  __shared__ R sNbW[EPB][2][NL][NN];        // primitives of the two neighbours in direction d
-  __shared__ R sWs[EPB][DIM][2][NL][NF];    // central face values w*
-  __shared__ R sD[NP][NP];
-  __shared__ R sLm[NP], sLp[NP], sIw[NP];
-  __shared__ ElemInfo<DIM, EPB> info;
+  __shared__ __attribute__((aligned(16))) R sW[NL][SL];        // nodal primitives (v, s)
+  __shared__ __attribute__((aligned(16))) R sX[DIM][NL][SL];   // per direction: gradients before the factor 2/h
+  __shared__ double sH2[EPB][DIM];
+  __shared__ int sNb[DIM][kStageNb<DIM, NP, R> ? EPB : 1][2];
 
   const long long S = msh.S;
-  if (tid < NP * NP) sD[tid / NP][tid % NP] = R(bas.Dhat[tid / NP][tid % NP]);
-  if (tid < NP) { sLm[tid] = R(bas.Lm[tid]); sLp[tid] = R(bas.Lp[tid]); sIw[tid] = R(bas.invw[tid]); }
-  elem_info<DIM, EPB>(info, msh, L, tid);
-  __syncthreads();
-
-  const int el = tid / NN, n = tid - (tid / NN) * NN;
-  const int e = el < EPB ? info.e[el] : -1;
-  const bool active = e >= 0;
-
-  double lfs = 0.0;  // global Lax-Friedrichs speed at this node (MODEL 1)
+  const auto& B = bas.of(R());
+  const NodeRole<DIM, NP, EPB> nr(tid);
+  const int pos = L * EPB + nr.el;
+  const bool active = nr.el < EPB && pos < msh.E;
+  const long long o = active ? (long long)msh.order[pos] * NN : 0;
+  Pair<double> u[NV];
   if (active) {
-    const long long o = (long long)e * NN + n;
-    double u[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) u[v] = U[v * S + o];
-    const double irho = 1.0 / u[0];
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) sW[el][d][n] = R(u[1 + d] * irho);
-    sW[el][DIM][n] = R(u[SI]);
-    if constexpr (MODEL == 1) lfs = lf_node_speed<DIM>(u, ph.T);
-  }
-  if constexpr (MODEL == 1) {
-    __shared__ double sRed[(Tile<DIM, NP, EPB>::THREADS + 63) / 64];
-    if (lfpart) block_max_store<Tile<DIM, NP, EPB>::THREADS>(lfs, sRed, lfpart + L, tid);
+    for (int v = 0; v < NV; ++v) u[v] = load_pair<NN>(U + v * S + o, nr.p);
   }
 
-  // the next direction's neighbour states are fetched into registers while
-  // the current direction's face values are formed
-  double nbu[2][NV];
-  auto fetch_nb = [&](auto dc) {
-    constexpr int dd = decltype(dc)::value;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const long long on = (long long)info.nb[el][dd][s] * NN + n;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) nbu[s][v] = U[v * S + on];
-    }
-  };
-  if (active) fetch_nb(std::integral_constant<int, 0>{});
-
-  // Per direction: stage the neighbours' primitives, then the central face
-  // values.  (Double-buffering the neighbours so that the face values of d
-  // share a phase with the staging of d+1 costs occupancy and was slower.)
-  auto stage = [&](auto dc) {
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int dir = wv / Tl::WPD;
+  const int sub = wv - dir * Tl::WPD, lane = tid & 63;
+  // the neighbours' traces: the weights of xi = +1 before the element, of xi = -1 after it
+  R wn[2][NL];
+  LineRole ln;
+  static_for<DIM>([&](auto dc) {
     constexpr int d = decltype(dc)::value;
-    if (active) {
+    if (dir != d) return;
+    ln = line_role<DIM, NP, EPB, d>(msh, L, sub, lane, nullptr);
+    if (ln.e >= 0 && ln.f == 0) sH2[ln.el][d] = ln.h2;
+    if constexpr (kStageNb<DIM, NP, R>) {
+      const NbPairs<DIM, NP, EPB> np(ln, sub, lane, sNb[d]);
+      const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+      static_for<2>([&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        Pair<double> x[Tl::RPC][NV];
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const double irho = 1.0 / nbu[s][0];
+        for (int r = 0; r < Tl::RPC; ++r)
+          if (np.at[r] >= 0) {
 #pragma unroll
-        for (int k = 0; k < DIM; ++k) sNbW[el][s][k][n] = R(nbu[s][1 + k] * irho);
-        sNbW[el][s][DIM][n] = R(nbu[s][SI]);
-      }
-      if constexpr (d + 1 < DIM) fetch_nb(std::integral_constant<int, d + 1>{});
-    }
-  };
-  auto faces = [&](auto dc) {
-    constexpr int d = decltype(dc)::value;
-    if (tid < EPB * 2 * NF) {
-      const int f = tid % NF;
-      const int s = (tid / NF) & 1;
-      const int le = tid / (2 * NF);
-      if (info.e[le] >= 0) {
-        const int base = face_base<NP>(d, f);
-        const int sd = dstride<NP>(d);
-        // on side + the element is the left state: the left trace takes the
-        // weights of xi = +1, the right one those of xi = -1
-        const R (*eL)[NN] = s ? sW[le] : sNbW[le][s];
-        const R (*eR)[NN] = s ? sNbW[le][s] : sW[le];
-        R wl[NL], wr[NL];
+            for (int v = 0; v < NV; ++v) x[r][v] = load_pair<NN>(U + v * S + (long long)np.nb[s][r] * NN, np.p[r]);
+          }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int k = 0; k < NL; ++k) { wl[k] = R(0); wr[k] = R(0); }
+        for (int r = 0; r < Tl::RPC; ++r)
+          if (np.at[r] >= 0) {
+            const double ia = 1.0 / x[r][0].a, ib = 1.0 / x[r][0].b;
 #pragma unroll
-        for (int l = 0; l < NP; ++l) {
-          const R Lp = sLp[l], Lm = sLm[l];
-          const int node = base + l * sd;
+            for (int k = 0; k < DIM; ++k) lds_put(&sX[d][k][np.at[r]], R(x[r][1 + k].a * ia), R(x[r][1 + k].b * ib));
+            lds_put(&sX[d][DIM][np.at[r]], R(x[r][SI].a), R(x[r][SI].b));
+          }
+        wave_fence();
+        if (ln.e >= 0) {
 #pragma unroll
           for (int k = 0; k < NL; ++k) {
-            wl[k] += Lp * eL[k][node];
-            wr[k] += Lm * eR[k][node];
+            wn[s][k] = R(0);
+#pragma unroll
+            for (int l = 0; l < NP; ++l) wn[s][k] += (s ? B.Lm[l] : B.Lp[l]) * sX[d][k][b0 + l * lds_step<NP>(d)];
           }
         }
+        wave_fence();
+      });
+      return;
+    }
+    if (ln.e < 0) return;
+    // every load of a line is issued before the first value is used
+    static_for<2>([&](auto sc) {
+      constexpr int s = decltype(sc)::value;
+      double x[NV][NP];
+      load_lines<NV, NP, dstride<NP>(d)>(U + (long long)ln.nb[s] * NN + ln.base, S, x);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int k = 0; k < NL; ++k) sWs[le][d][s][k][f] = R(0.5) * (wl[k] + wr[k]);
+      for (int k = 0; k < NL; ++k) wn[s][k] = R(0);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const double irho = 1.0 / x[0][l];
+        const R lw = s ? B.Lm[l] : B.Lp[l];
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) wn[s][k] += lw * R(x[1 + k][l] * irho);
+        wn[s][DIM] += lw * R(x[SI][l]);
       }
-    }
-  };
-  stage(std::integral_constant<int, 0>{});
-  __syncthreads();
-  static_for<DIM>([&](auto dc) {  // d-dependent index math is compile-time
-    constexpr int d = decltype(dc)::value;
-    faces(dc);
-    __syncthreads();
-    if constexpr (d + 1 < DIM) {
-      stage(std::integral_constant<int, d + 1>{});
-      __syncthreads();
-    }
+    });
   });
 
+  double lfs = 0.0;  // global Lax-Friedrichs speed at this pair (MODEL 1)
   if (active) {
-    R q[DIM][NL];
+    const double ia = 1.0 / u[0].a, ib = 1.0 / u[0].b;
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-      const int sd = dstride<NP>(d);
-      const int i = (n / sd) % NP;
-      const int f = face_of<NP>(d, n);
-      const R h2 = R(info.h2[el][d]);
+      lds_put(&sW[d][nr.sl], R(u[1 + d].a * ia), R(u[1 + d].b * ib));
+    }
+    lds_put(&sW[DIM][nr.sl], R(u[SI].a), R(u[SI].b));
+    if constexpr (MODEL == 1) {
+      double ua[NV], ub[NV];
 #pragma unroll
-      for (int k = 0; k < NL; ++k) {
+      for (int v = 0; v < NV; ++v) { ua[v] = u[v].a; ub[v] = u[v].b; }
+      lfs = fmax(lf_node_speed<DIM>(ua, ph.T), lf_node_speed<DIM>(ub, ph.T));
+    }
+  }
+  if constexpr (MODEL == 1) {
+    __shared__ double sRed[(Tl::THREADS + 63) / 64];
+    if (lfpart) block_max_store<Tl::THREADS>(lfs, sRed, lfpart + L, tid);
+  }
+  __syncthreads();
+
+  static_for<DIM>([&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (dir != d || ln.e < 0) return;
+    const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      R w[NP], wl = R(0), wr = R(0);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        w[l] = sW[k][b0 + l * lds_step<NP>(d)];
+        wl += B.Lp[l] * w[l];
+        wr += B.Lm[l] * w[l];
+      }
+      const R wsm = R(0.5) * (wn[0][k] + wr), wsp = R(0.5) * (wl + wn[1][k]);
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
         R vol = R(0);
 #pragma unroll
-        for (int l = 0; l < NP; ++l) vol += sD[i][l] * sW[el][k][n + (l - i) * sd];
-        const R surf = (sLp[i] * sWs[el][d][1][k][f] - sLm[i] * sWs[el][d][0][k][f]) * sIw[i];
-        q[d][k] = h2 * (surf - vol);
+        for (int l = 0; l < NP; ++l) vol += B.Dhat[i][l] * w[l];
+        const R surf = (B.Lp[i] * wsp - B.Lm[i] * wsm) * B.invw[i];
+        sX[d][k][b0 + i * lds_step<NP>(d)] = surf - vol;
       }
     }
-    R div = R(0);
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) div += q[d][d];
-    const long long o = (long long)e * NN + n;
+  });
+  __syncthreads();
+
+  if (active) {
+    R qd[2][DIM][NL], div[2];
     const R eps = R(ph.eps);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const R h2 = R(sH2[nr.el][d]);
+#pragma unroll
+      for (int k = 0; k < NL; ++k) {
+        const LdsPair<R> x = lds_get(&sX[d][k][nr.sl]);
+        qd[0][d][k] = h2 * x.a;
+        qd[1][d][k] = h2 * x.b;
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      div[h] = R(0);
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) div[h] += qd[h][d][d];
+    }
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
       for (int b = a; b < DIM; ++b) {
-        R t = eps * (q[b][a] + q[a][b]);
-        if (a == b) t -= eps * R(2.0 / 3.0) * div;
-        G[(long long)tau_index<DIM>(a, b) * S + o] = GT(t);
+        R t[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          t[h] = eps * (qd[h][b][a] + qd[h][a][b]);
+          if (a == b) t[h] -= eps * R(2.0 / 3.0) * div[h];
+        }
+        store_pair<NN>(G + (long long)tau_index<DIM>(a, b) * S + o, nr.p, GT(t[0]), GT(t[1]));
       }
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) G[(long long)(Sh::NTAU + d) * S + o] = GT(q[d][DIM]);
+    for (int d = 0; d < DIM; ++d)
+      store_pair<NN>(G + (long long)(Sh::NTAU + d) * S + o, nr.p, GT(qd[0][d][DIM]), GT(qd[1][d][DIM]));
   }
 }
 
@@ -433,86 +638,104 @@ __device__ __forceinline__ void lift_block(int L, int tid, const double* __restr
 // only read, so neighbouring workgroups see the first lifting's values.
 // -------------------------------------------------------------------------
 template <int DIM, int NP, int EPB>
-__device__ __forceinline__ void lap_block(int L, int tid, const double* __restrict__ U, double* __restrict__ G,
+__device__ __forceinline__ void lap_block_lines(int L, int tid, const double* __restrict__ U, double* __restrict__ G,
                                           const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph) {
   using Sh = Shape<DIM, NP>;
-  constexpr int NN = Sh::NN, NF = Sh::NF, NT = Sh::NTAU;
-  __shared__ double sg[EPB][NN];          // own g_d
-  __shared__ double sNb[EPB][2][NN];      // g_d of the two neighbours in direction d
-  __shared__ double sgs[EPB][2][NF];      // central face values on the two d-faces
-  __shared__ double sD[NP][NP];
-  __shared__ double sLm[NP], sLp[NP], sIw[NP];
-  __shared__ ElemInfo<DIM, EPB> info;
+  using Tl = Tile<DIM, NP, EPB>;
+  constexpr int NN = Sh::NN, NT = Sh::NTAU, SL = Tl::SL, PN = Tl::PN;
+  __shared__ __attribute__((aligned(16))) double sg[DIM][SL];   // own g_d; a d-line's lane overwrites it with the contribution to lap
+  __shared__ double sH2[EPB][DIM];
 
   const long long S = msh.S;
-  if (tid < NP * NP) sD[tid / NP][tid % NP] = bas.Dhat[tid / NP][tid % NP];
-  if (tid < NP) { sLm[tid] = bas.Lm[tid]; sLp[tid] = bas.Lp[tid]; sIw[tid] = bas.invw[tid]; }
-  elem_info<DIM, EPB>(info, msh, L, tid);
-  __syncthreads();
-
-  const int el = tid / NN, n = tid - (tid / NN) * NN;
-  const int e = el < EPB ? info.e[el] : -1;
-  const bool active = e >= 0;
-  const long long o = (long long)(active ? e : 0) * NN + n;
-
-  double g[DIM];
+  const auto& B = bas.of(double());
+  const NodeRole<DIM, NP, EPB> nr(tid);
+  const int pos = L * EPB + nr.el;
+  const bool active = nr.el < EPB && pos < msh.E;
+  const long long o = active ? (long long)msh.order[pos] * NN : 0;
+  Pair<double> g[DIM], tau[NT], rho{0.0, 0.0};
+  if (active) {
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) g[d] = active ? G[(long long)(NT + d) * S + o] : 0.0;
-  double lap = 0.0;
+    for (int d = 0; d < DIM; ++d) g[d] = load_pair<NN>(G + (long long)(NT + d) * S + o, nr.p);
+#pragma unroll
+    for (int k = 0; k < NT; ++k) tau[k] = load_pair<NN>(G + (long long)k * S + o, nr.p);
+    rho = load_pair<NN>(U + o, nr.p);
+  }
+
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int dir = wv / Tl::WPD;
+  const int sub = wv - dir * Tl::WPD, lane = tid & 63;
+  double gn[2] = {0.0, 0.0};
+  LineRole ln;
+  static_for<DIM>([&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (dir != d) return;
+    ln = line_role<DIM, NP, EPB, d>(msh, L, sub, lane, nullptr);
+    if (ln.e < 0) return;
+    if (ln.f == 0) sH2[ln.el][d] = ln.h2;
+    double x[2][1][NP];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      load_lines<1, NP, dstride<NP>(d)>(G + (long long)(NT + d) * S + (long long)ln.nb[s] * NN + ln.base, S, x[s]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int l = 0; l < NP; ++l) gn[s] += (s ? B.Lm[l] : B.Lp[l]) * x[s][0][l];
+  });
+  if (active) {
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      lds_put(&sg[d][nr.sl], g[d].a, g[d].b);
+    }
+  }
+  __syncthreads();
 
   static_for<DIM>([&](auto dc) {
     constexpr int d = decltype(dc)::value;
-    if (active) {
-      sg[el][n] = g[d];
+    if (dir != d || ln.e < 0) return;
+    const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+    double w[NP], wl = 0.0, wr = 0.0;
 #pragma unroll
-      for (int s = 0; s < 2; ++s) sNb[el][s][n] = G[(long long)(NT + d) * S + (long long)info.nb[el][d][s] * NN + n];
+    for (int l = 0; l < NP; ++l) {
+      w[l] = sg[d][b0 + l * lds_step<NP>(d)];
+      wl += B.Lp[l] * w[l];
+      wr += B.Lm[l] * w[l];
     }
-    __syncthreads();
-    if (tid < EPB * 2 * NF) {
-      const int f = tid % NF;
-      const int s = (tid / NF) & 1;
-      const int le = tid / (2 * NF);
-      if (info.e[le] >= 0) {
-        const int base = face_base<NP>(d, f);
-        const int sd = dstride<NP>(d);
-        double own = 0.0, oth = 0.0;
+    const double gm = 0.5 * (wr + gn[0]), gp = 0.5 * (wl + gn[1]);
 #pragma unroll
-        for (int l = 0; l < NP; ++l) {
-          const int node = base + l * sd;
-          own += (s ? sLp[l] : sLm[l]) * sg[le][node];
-          oth += (s ? sLm[l] : sLp[l]) * sNb[le][s][node];
-        }
-        sgs[le][s][f] = 0.5 * (own + oth);
-      }
-    }
-    __syncthreads();
-    if (active) {
-      const int sd = dstride<NP>(d);
-      const int i = (n / sd) % NP;
-      const int f = face_of<NP>(d, n);
+    for (int i = 0; i < NP; ++i) {
       double vol = 0.0;
 #pragma unroll
-      for (int l = 0; l < NP; ++l) vol += sD[i][l] * sg[el][n + (l - i) * sd];
-      const double surf = (sLp[i] * sgs[el][1][f] - sLm[i] * sgs[el][0][f]) * sIw[i];
-      lap += info.h2[el][d] * (surf - vol);
+      for (int l = 0; l < NP; ++l) vol += B.Dhat[i][l] * w[l];
+      const double surf = (B.Lp[i] * gp - B.Lm[i] * gm) * B.invw[i];
+      sg[d][b0 + i * lds_step<NP>(d)] = surf - vol;
     }
-    __syncthreads();  // LDS reused by the next direction
   });
+  __syncthreads();
 
   if (active) {
-    const double rho = U[o];
-    double g2 = 0.0;
+    double iso[2], lap[2] = {0.0, 0.0}, g2[2] = {0.0, 0.0};
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) g2 += g[d] * g[d];
-    const double iso = ph.kappa * (rho * lap + 0.5 * g2);
+    for (int d = 0; d < DIM; ++d) {
+      const LdsPair<double> x = lds_get(&sg[d][nr.sl]);
+      lap[0] += sH2[nr.el][d] * x.a;
+      lap[1] += sH2[nr.el][d] * x.b;
+      g2[0] += g[d].a * g[d].a;
+      g2[1] += g[d].b * g[d].b;
+    }
+    iso[0] = ph.kappa * (rho.a * lap[0] + 0.5 * g2[0]);
+    iso[1] = ph.kappa * (rho.b * lap[1] + 0.5 * g2[1]);
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
       for (int b = a; b < DIM; ++b) {
-        const long long ot = (long long)tau_index<DIM>(a, b) * S + o;
-        double t = G[ot] - ph.kappa * g[a] * g[b];
-        if (a == b) t += iso;
-        G[ot] = t;
+        const int k = tau_index<DIM>(a, b);
+        double ta = tau[k].a - ph.kappa * g[a].a * g[b].a, tb = tau[k].b - ph.kappa * g[a].b * g[b].b;
+        if (a == b) {
+          ta += iso[0];
+          tb += iso[1];
+        }
+        store_pair<NN>(G + (long long)k * S + o, nr.p, ta, tb);
       }
   }
 }
@@ -526,316 +749,480 @@ __device__ __forceinline__ void lap_block(int L, int tid, const double* __restri
 // second-order stress Sigma in G's tau slots and no source; then
 //   dU <- A dU + dt R,  U <- U + B dU.
 // -------------------------------------------------------------------------
+
+// Numerical flux of direction d between the traces (uL, vL) and (uR, vR), rL
+// and rR the FP64 traces of the density.
+template <int DIM, typename R, int FLUX, int MODEL, int d, int NV, int NVX>
+__device__ __forceinline__ void face_flux(const R* uL, const R* uR, const R* vL, const R* vR, double rL, double rR,
+                                          R lam_g, R kb, const PhysArgs& ph, R* Fs) {
+  R paL, paR, aL = R(0), aR = R(0);
+  if constexpr (FLUX == 2) {
+    // the global Lax-Friedrichs flux needs no local sound speed
+    paL = p_alpha_guarded<R>(rL, ph);
+    paR = p_alpha_guarded<R>(rR, ph);
+  } else {
+    p_alpha_sound_guarded<R>(rL, ph, paL, aL);
+    p_alpha_sound_guarded<R>(rR, ph, paR, aR);
+  }
+  const R irL = R(1) / uL[0], irR = R(1) / uR[0];
+  R FL[NV], FR[NV], Fc[NV];
+  conv_flux<DIM, R, NV>(d, uL, irL, paL, FL);
+  conv_flux<DIM, R, NV>(d, uR, irR, paR, FR);
+  if constexpr (FLUX == 2) {
+    // global Lax-Friedrichs: one dissipation speed for the whole grid
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Fc[v] = R(0.5) * (FL[v] + FR[v]) - R(0.5) * lam_g * (uR[v] - uL[v]);
+  } else if constexpr (FLUX == 0) {
+    // Rusanov: central flux minus the larger wave speed times the jump
+    const R sL = fabs(uL[1 + d] * irL) + aL;
+    const R sR = fabs(uR[1 + d] * irR) + aR;
+    const R lam = sL > sR ? sL : sR;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const R diss = (v == NV - 1 && !ph.diss_c) ? R(0) : lam * (uR[v] - uL[v]);
+      Fc[v] = R(0.5) * (FL[v] + FR[v]) - R(0.5) * diss;
+    }
+  } else {
+    // HLLC of the barotropic convective part: Davis speeds; HLL flux for
+    // mass and normal momentum; tangential momenta carried by the mass
+    // flux with the velocity of the upwind side of the contact
+    // S* = F_hll[rho] / rho_hll; HLL dissipation alone on c
+    const R vnL = uL[1 + d] * irL, vnR = uR[1 + d] * irR;
+    const R SL = fmin(vnL - aL, vnR - aR), SR = fmax(vnL + aL, vnR + aR);
+    if (SL >= R(0)) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Fc[v] = FL[v];
+    } else if (SR <= R(0)) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Fc[v] = FR[v];
+    } else {
+      const R w = R(1) / (SR - SL);
+      const R Fm = (SR * FL[0] - SL * FR[0] + SL * SR * (uR[0] - uL[0])) * w;
+      const R rh = (SR * uR[0] - SL * uL[0] - (FR[0] - FL[0])) * w;
+      const bool left = Fm / rh >= R(0);
+      Fc[0] = Fm;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        if (j == d)
+          Fc[1 + j] = (SR * FL[1 + j] - SL * FR[1 + j] + SL * SR * (uR[1 + j] - uL[1 + j])) * w;
+        else
+          Fc[1 + j] = Fm * (left ? uL[1 + j] * irL : uR[1 + j] * irR);
+      }
+      Fc[NV - 1] = ph.diss_c ? SL * SR * (uR[NV - 1] - uL[NV - 1]) * w : R(0);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    Fs[v] = Fc[v];
+    if (v >= 1 && v <= DIM) Fs[v] -= R(0.5) * (vL[v - 1] + vR[v - 1]);
+    if constexpr (MODEL == 0) {
+      if (v == NV - 1) Fs[v] -= R(0.5) * kb * (vL[DIM] + vR[DIM]);
+    }
+  }
+}
+
+constexpr int kLineGroup = 3;
+
+template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX, int MODEL>
+__device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __restrict__ U, const GT* __restrict__ G,
+                                          double* __restrict__ Uout, double* __restrict__ dU, const BasisArgs& bas,
+                                          const MeshArgs& msh, const PhysArgs& ph, const StageArgs& st) {
+  using Sh = Shape<DIM, NP>;
+  using Tl = Tile<DIM, NP, EPB>;
+  constexpr int NN = Sh::NN, NT = Sh::NTAU, SL = Tl::SL, PN = Tl::PN;
+  constexpr int NV = MODEL == 1 ? DIM + 1 : DIM + 2;   // conserved variables
+  constexpr int NG = MODEL == 1 ? NT : Sh::NG;         // G slots read: Sigma, or (tau, grad c)
+  constexpr int NVX = MODEL == 1 ? DIM : DIM + 1;      // viscous flux components of one direction
+  static_assert(MODEL == 0 || FLUX == 2, "the original NSK path uses the global Lax-Friedrichs flux");
+  constexpr bool MIXED = sizeof(R) != sizeof(double);
+  // own values: U, G, p_alpha, 1/rho; once every line is in registers the
+  // same memory takes the directions' contributions
+  constexpr int IP = NV + NG, II = IP + 1;
+  constexpr int ROWS = cmax(NV + NG + 2, DIM * NV);
+  constexpr bool STAGE = kStageNb<DIM, NP, R>;
+  constexpr int RPD = ROWS / DIM;  // rows in which a direction's waves stage neighbours
+  static_assert(!STAGE || (RPD >= NV && RPD >= NVX), "staging rows");
+  __shared__ __attribute__((aligned(16))) R sIn[ROWS][SL];
+  __shared__ __attribute__((aligned(16))) double sRho64[MIXED ? (STAGE ? DIM : 1) : 1][MIXED ? SL : 1];  // FP64 densities (mixed precision only)
+  __shared__ int sNb[DIM][STAGE ? EPB : 1][2];
+  __shared__ double sH2[EPB][DIM];
+  __shared__ int sE[EPB];  // element of each slot, -1: none
+
+  const long long S = msh.S;
+  const auto& B = bas.of(R());
+  const NodeRole<DIM, NP, EPB> nr(tid);
+  const int pos = L * EPB + nr.el;
+  int e = nr.el < EPB && pos < msh.E ? msh.order[pos] : -1;
+  // elements on FV sub-cells are updated by their own kernel: treat them as absent
+  if (st.skip && e >= 0 && st.skip[e]) e = -1;
+  const R kb = R(ph.kb);
+  const R lam_g = FLUX == 2 ? R(*st.lf) : R(0);  // global Lax-Friedrichs speed
+  if (nr.el < EPB && nr.p == 0) sE[nr.el] = e;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int dir = wv / Tl::WPD;
+  const int sub = wv - dir * Tl::WPD, lane = tid & 63;
+  Pair<double> u0[NV];
+  Pair<GT> g0[NG];
+  auto load_own = [&]() {
+    if (e < 0) return;
+    const long long o = (long long)e * NN;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) u0[v] = load_pair<NN>(U + v * S + o, nr.p);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) g0[k] = load_pair<NN>(G + (long long)k * S + o, nr.p);
+  };
+  auto put_own = [&]() {
+    if (e < 0) return;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) lds_put(&sIn[v][nr.sl], R(u0[v].a), R(u0[v].b));
+#pragma unroll
+    for (int k = 0; k < NG; ++k) lds_put(&sIn[NV + k][nr.sl], R(g0[k].a), R(g0[k].b));
+    lds_put(&sIn[IP][nr.sl], p_alpha_guarded<R>(u0[0].a, ph), p_alpha_guarded<R>(u0[0].b, ph));
+    lds_put(&sIn[II][nr.sl], R(1) / R(u0[0].a), R(1) / R(u0[0].b));
+    if (MIXED) lds_put(&sRho64[0][MIXED ? nr.sl : 0], u0[0].a, u0[0].b);
+  };
+  if constexpr (!STAGE) {
+    load_own();
+    put_own();
+  }
+
+  // line role: the neighbours' traces
+  R un[2][NV], vn[2][NVX];
+  double rn[2] = {0.0, 0.0};  // density traces in FP64 (EoS guard)
+  LineRole ln;
+  static_for<DIM>([&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (dir != d) return;
+    ln = line_role<DIM, NP, EPB, d>(msh, L, sub, lane, st.skip);
+    if (ln.e >= 0 && ln.f == 0) sH2[ln.el][d] = ln.h2;
+    if constexpr (STAGE) {
+      // U, then the viscous components, of each side, in the rows of the
+      // direction; the loads run two batches ahead
+      const NbPairs<DIM, NP, EPB> np(ln, sub, lane, sNb[d]);
+      const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+      Pair<double> xu[Tl::RPC][NV];
+      Pair<GT> xg[Tl::RPC][NVX];
+      auto load_u = [&](int s) {
+#pragma unroll
+        for (int r = 0; r < Tl::RPC; ++r)
+          if (np.at[r] >= 0) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) xu[r][v] = load_pair<NN>(U + v * S + (long long)np.nb[s][r] * NN, np.p[r]);
+          }
+      };
+      auto load_g = [&](int s) {
+#pragma unroll
+        for (int r = 0; r < Tl::RPC; ++r)
+          if (np.at[r] >= 0) {
+#pragma unroll
+            for (int k = 0; k < NVX; ++k)
+              xg[r][k] = load_pair<NN>(
+                  G + (long long)(k < DIM ? tau_index<DIM>(k, d) : NT + d) * S + (long long)np.nb[s][r] * NN, np.p[r]);
+          }
+      };
+      auto fold_u = [&](int s) {
+#pragma unroll
+        for (int r = 0; r < Tl::RPC; ++r)
+          if (np.at[r] >= 0) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) lds_put(&sIn[d * RPD + v][np.at[r]], R(xu[r][v].a), R(xu[r][v].b));
+            if constexpr (MIXED) lds_put(&sRho64[d][np.at[r]], xu[r][0].a, xu[r][0].b);
+          }
+        wave_fence();
+        if (ln.e >= 0) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) {
+            un[s][v] = R(0);
+#pragma unroll
+            for (int l = 0; l < NP; ++l)
+              un[s][v] += (s ? B.Lm[l] : B.Lp[l]) * sIn[d * RPD + v][b0 + l * lds_step<NP>(d)];
+          }
+          if constexpr (MIXED) {
+#pragma unroll
+            for (int l = 0; l < NP; ++l)
+              rn[s] += (s ? bas.d.Lm[l] : bas.d.Lp[l]) * sRho64[d][b0 + l * lds_step<NP>(d)];
+          }
+        }
+        wave_fence();
+      };
+      auto fold_g = [&](int s) {
+#pragma unroll
+        for (int r = 0; r < Tl::RPC; ++r)
+          if (np.at[r] >= 0) {
+#pragma unroll
+            for (int k = 0; k < NVX; ++k) lds_put(&sIn[d * RPD + k][np.at[r]], R(xg[r][k].a), R(xg[r][k].b));
+          }
+        wave_fence();
+        if (ln.e >= 0) {
+#pragma unroll
+          for (int k = 0; k < NVX; ++k) {
+            vn[s][k] = R(0);
+#pragma unroll
+            for (int l = 0; l < NP; ++l)
+              vn[s][k] += (s ? B.Lm[l] : B.Lp[l]) * sIn[d * RPD + k][b0 + l * lds_step<NP>(d)];
+          }
+        }
+        wave_fence();
+      };
+      load_u(0);
+      load_g(0);
+      __builtin_amdgcn_sched_barrier(0);
+      fold_u(0);
+      load_u(1);
+      __builtin_amdgcn_sched_barrier(0);
+      fold_g(0);
+      load_g(1);
+      __builtin_amdgcn_sched_barrier(0);
+      fold_u(1);
+      fold_g(1);
+      return;
+    }
+    if (ln.e < 0) return;
+    // components in groups of kLineGroup, the loads of a group issued two
+    // groups before their use
+    constexpr int NC = NV + NVX, NGRP = (2 * NC + kLineGroup - 1) / kLineGroup;
+    double xu[2 * kLineGroup][NP];
+    GT xg[2 * kLineGroup][NP];
+    static_for<NGRP + 2>([&](auto gc) {
+      constexpr int g = decltype(gc)::value;
+      static_for<kLineGroup>([&](auto jc) {
+        constexpr int it = (g - 2) * kLineGroup + decltype(jc)::value;
+        if constexpr (it >= 0 && it < 2 * NC) {
+          constexpr int s = it / NC, k = it % NC, slot = it % (2 * kLineGroup);
+          R a = R(0);
+#pragma unroll
+          for (int l = 0; l < NP; ++l) {
+            if constexpr (k < NV) {
+              a += (s ? B.Lm[l] : B.Lp[l]) * R(xu[slot][l]);
+              if (MIXED && k == 0) rn[s] += (s ? bas.d.Lm[l] : bas.d.Lp[l]) * xu[slot][l];
+            } else {
+              a += (s ? B.Lm[l] : B.Lp[l]) * R(xg[slot][l]);
+            }
+          }
+          if constexpr (k < NV) un[s][k] = a;
+          else vn[s][k - NV] = a;
+        }
+      });
+      static_for<kLineGroup>([&](auto jc) {
+        constexpr int it = g * kLineGroup + decltype(jc)::value;
+        if constexpr (it < 2 * NC) {
+          constexpr int s = it / NC, k = it % NC, slot = it % (2 * kLineGroup);
+          const long long on = (long long)ln.nb[s] * NN + ln.base;
+          if constexpr (k < NV) {
+#pragma unroll
+            for (int l = 0; l < NP; ++l) xu[slot][l] = (U + k * S + on)[l * dstride<NP>(d)];
+          } else {
+            constexpr int gk = k - NV < DIM ? tau_index<DIM>(k - NV < DIM ? k - NV : 0, d) : NT + d;
+#pragma unroll
+            for (int l = 0; l < NP; ++l) xg[slot][l] = (G + (long long)gk * S + on)[l * dstride<NP>(d)];
+          }
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  });
+  if constexpr (STAGE) {
+    load_own();
+    __syncthreads();  // the neighbours are folded: their rows take the own values
+    put_own();
+  }
+  __syncthreads();
+
+  // line role: numerical fluxes at both ends, contraction of the nodal flux
+  R t[NP][NV];
+  static_for<DIM>([&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (dir != d || ln.e < 0) return;
+    const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+    // own traces at both ends (0: xi = -1, 1: xi = +1), one pass over the line
+    R uo[2][NV], vo[2][NVX], Fs[2][NV];
+    double ro[2] = {0.0, 0.0};
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      uo[0][v] = uo[1][v] = R(0);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const R x = sIn[v][b0 + l * lds_step<NP>(d)];
+        uo[0][v] += B.Lm[l] * x;
+        uo[1][v] += B.Lp[l] * x;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NVX; ++k) {
+      vo[0][k] = vo[1][k] = R(0);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const R x = sIn[NV + (k < DIM ? tau_index<DIM>(k, d) : NT + d)][b0 + l * lds_step<NP>(d)];
+        vo[0][k] += B.Lm[l] * x;
+        vo[1][k] += B.Lp[l] * x;
+      }
+    }
+    if constexpr (MIXED) {
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const double x = sRho64[0][b0 + l * lds_step<NP>(d)];
+        ro[0] += bas.d.Lm[l] * x;
+        ro[1] += bas.d.Lp[l] * x;
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        ro[s] = uo[s][0];
+        rn[s] = un[s][0];
+      }
+    }
+    face_flux<DIM, R, FLUX, MODEL, d, NV, NVX>(un[0], uo[0], vn[0], vo[0], rn[0], ro[0], lam_g, kb, ph, Fs[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    face_flux<DIM, R, FLUX, MODEL, d, NV, NVX>(uo[1], un[1], vo[1], vn[1], ro[1], rn[1], lam_g, kb, ph, Fs[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    // the line is read again for the volume term rather than held in registers
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) t[i][v] = R(0);
+#pragma unroll
+    for (int l = 0; l < NP; ++l) {
+      const int b = b0 + l * lds_step<NP>(d);
+      R u[NV], F[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) u[v] = sIn[v][b];
+      conv_flux<DIM, R, NV>(d, u, sIn[II][b], sIn[IP][b], F);
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) F[1 + j] -= sIn[NV + tau_index<DIM>(j, d)][b];
+      if constexpr (MODEL == 0) F[DIM + 1] -= kb * sIn[NV + NT + d][b];
+#pragma unroll
+      for (int i = 0; i < NP; ++i)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) t[i][v] += B.Dhat[i][l] * F[v];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) t[i][v] = t[i][v] - (B.wp[i] * Fs[1][v] - B.wm[i] * Fs[0][v]);
+    }
+  });
+  __syncthreads();  // every line is read: sIn takes the contributions
+  static_for<DIM>([&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (dir != d || ln.e < 0) return;
+    const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) sIn[d * NV + v][b0 + i * lds_step<NP>(d)] = t[i][v];
+  });
+
+  // the pair's place and values are taken again rather than kept in registers
+  // over the line phase, which would cost a wave per SIMD
+  const NodeRole<DIM, NP, EPB> nu(opaque(tid));
+  const int eu = nu.el < EPB ? sE[nu.el] : -1;
+  const long long o = (long long)cmax(eu, 0) * NN;
+  Pair<double> u[NV], du_old[NV];
+  Pair<GT> gc[DIM];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) du_old[v] = Pair<double>{0.0, 0.0};
+  if (eu >= 0) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) u[v] = load_pair<NN>(U + v * S + o, nu.p);
+    if (st.mode == 1 && st.A != 0.0) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) du_old[v] = load_pair<NN>(dU + v * S + o, nu.p);
+    }
+    if constexpr (MODEL == 0) {
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) gc[d] = load_pair<NN>(G + (long long)(NT + d) * S + o, nu.p);
+    }
+  }
+  __syncthreads();
+
+  // source (FP64) and update
+  if (eu >= 0) {
+    double Rv[2][NV];
+    {
+      R acc[2][NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) acc[0][v] = acc[1][v] = R(0);
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) {
+        const R h2 = R(sH2[nu.el][d]);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          const LdsPair<R> x = lds_get(&sIn[d * NV + v][nu.sl]);
+          acc[0][v] += h2 * x.a;
+          acc[1][v] += h2 * x.b;
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        Rv[0][v] = double(acc[0][v]);
+        Rv[1][v] = double(acc[1][v]);
+      }
+    }
+    if constexpr (MODEL == 0) {
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) {
+        Rv[0][1 + d] += ph.alpha * u[0].a * double(R(gc[d].a));
+        Rv[1][1 + d] += ph.alpha * u[0].b * double(R(gc[d].b));
+      }
+      Rv[0][DIM + 1] += ph.ab * (u[0].a - u[DIM + 1].a);
+      Rv[1][DIM + 1] += ph.ab * (u[0].b - u[DIM + 1].b);
+      if (st.closure) {
+#pragma unroll
+        for (int d = 0; d <= DIM; ++d) {
+          const Pair<float> x = load_pair<NN>(st.closure + d * S + o, nu.p);
+          Rv[0][1 + d] += double(x.a);
+          Rv[1][1 + d] += double(x.b);
+        }
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      if (st.mode == 0) {
+        store_pair<NN>(Uout + v * S + o, nu.p, Rv[0][v], Rv[1][v]);
+      } else {
+        const double da = st.A * du_old[v].a + st.dt * Rv[0][v], db = st.A * du_old[v].b + st.dt * Rv[1][v];
+        store_pair<NN>(dU + v * S + o, nu.p, da, db);
+        store_pair<NN>(Uout + v * S + o, nu.p, u[v].a + st.B * da, u[v].b + st.B * db);
+      }
+    }
+  }
+}
+
+}  // namespace nsk
+
+#include "dg_1d.hpp"
+
+namespace nsk {
+
+template <int DIM, int NP, int EPB, typename R, typename GT, int MODEL = 0>
+__device__ __forceinline__ void lift_block(int L, int tid, const double* __restrict__ U, GT* __restrict__ G,
+                                           const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph,
+                                           double* __restrict__ lfpart = nullptr) {
+  if constexpr (DIM == 1)
+    lift_block_1d<NP, EPB, R, GT, MODEL>(L, tid, U, G, bas, msh, ph, lfpart);
+  else
+    lift_block_lines<DIM, NP, EPB, R, GT, MODEL>(L, tid, U, G, bas, msh, ph, lfpart);
+}
+
+template <int DIM, int NP, int EPB>
+__device__ __forceinline__ void lap_block(int L, int tid, const double* __restrict__ U, double* __restrict__ G,
+                                          const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph) {
+  if constexpr (DIM == 1)
+    lap_block_1d<NP, EPB>(L, tid, U, G, bas, msh, ph);
+  else
+    lap_block_lines<DIM, NP, EPB>(L, tid, U, G, bas, msh, ph);
+}
+
 template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX = 0, int MODEL = 0>
 __device__ __forceinline__ void rhs_block(int L, int tid, const double* __restrict__ U, const GT* __restrict__ G,
                                           double* __restrict__ Uout, double* __restrict__ dU, const BasisArgs& bas,
                                           const MeshArgs& msh, const PhysArgs& ph, const StageArgs& st) {
-  using Sh = Shape<DIM, NP>;
-  constexpr int NN = Sh::NN, NF = Sh::NF, NT = Sh::NTAU;
-  constexpr int NV = MODEL == 1 ? DIM + 1 : DIM + 2;   // conserved variables
-  constexpr int NG = MODEL == 1 ? NT : Sh::NG;         // G slots read: Sigma, or (tau, grad c)
-  constexpr int NVX = MODEL == 1 ? DIM : DIM + 1;      // viscous flux components of one direction
-  constexpr int NX = NV + NVX;              // per node: U and the viscous flux components of direction d
-  static_assert(MODEL == 0 || FLUX == 2, "the original NSK path uses the global Lax-Friedrichs flux");
-  constexpr bool MIXED = sizeof(R) != sizeof(double);
-  constexpr int R64E = MIXED ? EPB : 1, R64N = MIXED ? NN : 1;
-  __shared__ R sOwn[EPB][NX][NN];           // own U and (tau_{.d}, dc/dx_d)
-  __shared__ R sNb[EPB][2][NX][NN];         // the same for the two neighbours in direction d
-  __shared__ double sRho64[R64E][3][R64N];  // FP64 densities (mixed precision only)
-  // The nodal flux is double-buffered by direction (so that the
-  // accumulation of d and the staging of d+1 share a phase) only where the
-  // second buffer costs no workgroup per CU, or where at least 5 still fit
-  // (measured: the original NSK kernel runs faster pipelined at 5 per CU than
-  // with one buffer at 6); otherwise one buffer and one more barrier per
-  // direction.
-  constexpr int kLdsCu = 163840;
-  constexpr int LDS_FIXED = int(sizeof(R)) * (EPB * 3 * NX * NN + EPB * 2 * NV * NF + NP * NP + 3 * NP) +
-                            int(sizeof(double)) * R64E * 3 * R64N + int(sizeof(ElemInfo<DIM, EPB>));
-  constexpr int LDS_F = int(sizeof(R)) * EPB * NV * NN;
-  constexpr bool PIPE = kLdsCu / (LDS_FIXED + 2 * LDS_F) == kLdsCu / (LDS_FIXED + LDS_F) ||
-                        kLdsCu / (LDS_FIXED + 2 * LDS_F) >= 5;
-  __shared__ R sF[PIPE ? 2 : 1][EPB][NV][NN];  // total flux Fc_d - Fv_d
-  __shared__ R sFs[EPB][2][NV][NF];         // numerical flux on the two d-faces
-  __shared__ R sD[NP][NP];
-  __shared__ R sLm[NP], sLp[NP], sIw[NP];
-  __shared__ ElemInfo<DIM, EPB> info;
-
-  const long long S = msh.S;
-  if (tid < NP * NP) sD[tid / NP][tid % NP] = R(bas.Dhat[tid / NP][tid % NP]);
-  if (tid < NP) { sLm[tid] = R(bas.Lm[tid]); sLp[tid] = R(bas.Lp[tid]); sIw[tid] = R(bas.invw[tid]); }
-  elem_info<DIM, EPB>(info, msh, L, tid);
-  // elements on FV sub-cells are updated by their own kernel: treat them as absent
-  if (st.skip && tid < EPB && info.e[tid] >= 0 && st.skip[info.e[tid]]) info.e[tid] = -1;
-  __syncthreads();
-
-  const int el = tid / NN, n = tid - (tid / NN) * NN;
-  const int e = el < EPB ? info.e[el] : -1;
-  const bool active = e >= 0;
-  const long long o = (long long)(active ? e : 0) * NN + n;
-  const R kb = R(ph.kb);
-
-  double rho64 = 0.0, c64 = 0.0;
-  const R lam_g = FLUX == 2 ? R(*st.lf) : R(0);  // global Lax-Friedrichs speed
-  double u64[NV], du_old[NV];
-  R u[NV], g[NG];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) { u64[v] = 0.0; du_old[v] = 0.0; u[v] = R(0); }
-#pragma unroll
-  for (int k = 0; k < NG; ++k) g[k] = R(0);
-  if (active) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) u64[v] = U[v * S + o];
-#pragma unroll
-    for (int k = 0; k < NG; ++k) g[k] = R(G[(long long)k * S + o]);
-    // FP64: the register is read early (occupancy is held at 2 waves per
-    // SIMD by the LDS anyway); mixed precision reads it at the update,
-    // which keeps the kernel under 168 VGPRs (3 waves per SIMD)
-    if (!MIXED && st.mode == 1 && st.A != 0.0) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) du_old[v] = dU[v * S + o];
-    }
-    rho64 = u64[0];
-    if constexpr (MODEL == 0) c64 = u64[DIM + 1];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) { u[v] = R(u64[v]); sOwn[el][v][n] = u[v]; }
-    if (MIXED) sRho64[MIXED ? el : 0][0][MIXED ? n : 0] = rho64;
-  }
-  R pa = R(0), irho = R(0);
-  if (active) {
-    pa = p_alpha_guarded<R>(rho64, ph);
-    irho = R(1) / u[0];
-  }
-  R acc[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) acc[v] = R(0);
-
-  // Neighbour values of one direction (U and the direction's viscous
-  // components) in registers.  In FP64 model II the LDS holds the kernel at
-  // 2 waves per SIMD whatever its register count, so the next direction's
-  // values are fetched while the current one is computed.  The
-  // mixed-precision kernel (3 waves per SIMD) and the original NSK path
-  // (whose smaller LDS tile allows 5 elements per CU at 3 waves per SIMD,
-  // which the prefetch's registers would forbid) fetch them when they stage
-  // them; the HLLC face code needs the registers.
-  constexpr bool PREFETCH = !MIXED && FLUX != 1 && MODEL == 0;
-  double nbv[2][NX];
-  auto fetch_nb = [&](auto dc) {
-    constexpr int dd = decltype(dc)::value;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const long long on = (long long)info.nb[el][dd][s] * NN + n;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) nbv[s][v] = U[v * S + on];
-#pragma unroll
-      for (int j = 0; j < DIM; ++j) nbv[s][NV + j] = double(G[(long long)tau_index<DIM>(j, dd) * S + on]);
-      if constexpr (MODEL == 0) nbv[s][NV + DIM] = double(G[(long long)(NT + dd) * S + on]);
-    }
-  };
-  if (PREFETCH && active) fetch_nb(std::integral_constant<int, 0>{});
-
-  // Per direction: stage (own viscous components, nodal flux, neighbours),
-  // faces (numerical fluxes), accumulate (volume and surface terms).  The
-  // accumulation of direction d and the staging of d+1 share a phase: the
-  // nodal flux alternates between two buffers, and everything else staging
-  // writes is read only by the face phase before it.
-  auto stage = [&](auto dc) {  // d-dependent index math is compile-time
-    constexpr int d = decltype(dc)::value;
-    if (active) {
-      // own viscous components of direction d and the nodal total flux
-#pragma unroll
-      for (int j = 0; j < DIM; ++j) sOwn[el][NV + j][n] = g[tau_index<DIM>(j, d)];
-      if constexpr (MODEL == 0) sOwn[el][NV + DIM][n] = g[NT + d];
-      R F[NV];
-      conv_flux<DIM, R, NV>(d, u, irho, pa, F);
-#pragma unroll
-      for (int j = 0; j < DIM; ++j) F[1 + j] -= g[tau_index<DIM>(j, d)];
-      if constexpr (MODEL == 0) F[DIM + 1] -= kb * g[NT + d];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) sF[PIPE ? (d & 1) : 0][el][v][n] = F[v];
-      // the two neighbours, coalesced
-      if (!PREFETCH) fetch_nb(dc);
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        if (MIXED) sRho64[MIXED ? el : 0][1 + s][MIXED ? n : 0] = nbv[s][0];
-#pragma unroll
-        for (int x = 0; x < NX; ++x) sNb[el][s][x][n] = R(nbv[s][x]);
-      }
-      if constexpr (PREFETCH && d + 1 < DIM) fetch_nb(std::integral_constant<int, d + 1>{});
-    }
-  };
-  auto faces = [&](auto dc) {
-    constexpr int d = decltype(dc)::value;
-    if (tid < EPB * 2 * NF) {
-      const int f = tid % NF;
-      const int s = (tid / NF) & 1;
-      const int le = tid / (2 * NF);
-      if (info.e[le] >= 0) {
-        const int base = face_base<NP>(d, f);
-        const int sd = dstride<NP>(d);
-        // left/right in direction d: on side + this element is the left
-        // state.  The left trace takes the weights of xi = +1, the right one
-        // those of xi = -1, so only the two source elements depend on s.
-        const R (*eL)[NN] = s ? sOwn[le] : sNb[le][s];
-        const R (*eR)[NN] = s ? sNb[le][s] : sOwn[le];
-        const int qL = s ? 0 : 1, qR = s ? 2 : 0;  // FP64 density slots (mixed precision)
-        double rL = 0.0, rR = 0.0;  // density traces in FP64 (EoS guard)
-        R uL[NV], uR[NV], vL[NVX], vR[NVX];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) { uL[v] = R(0); uR[v] = R(0); }
-#pragma unroll
-        for (int k = 0; k < NVX; ++k) { vL[k] = R(0); vR[k] = R(0); }
-#pragma unroll
-        for (int l = 0; l < NP; ++l) {
-          const int node = base + l * sd;
-          const R Lp = sLp[l], Lm = sLm[l];
-          const double xl = MIXED ? sRho64[MIXED ? le : 0][MIXED ? qL : 0][MIXED ? node : 0] : double(eL[0][node]);
-          const double xr = MIXED ? sRho64[MIXED ? le : 0][MIXED ? qR : 0][MIXED ? node : 0] : double(eR[0][node]);
-          rL += bas.Lp[l] * xl;
-          rR += bas.Lm[l] * xr;
-#pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            uL[v] += Lp * eL[v][node];
-            uR[v] += Lm * eR[v][node];
-          }
-#pragma unroll
-          for (int k = 0; k < NVX; ++k) {
-            vL[k] += Lp * eL[NV + k][node];
-            vR[k] += Lm * eR[NV + k][node];
-          }
-        }
-        R paL, paR, aL = R(0), aR = R(0);
-        if constexpr (FLUX == 2) {
-          // the global Lax-Friedrichs flux needs no local sound speed
-          paL = p_alpha_guarded<R>(rL, ph);
-          paR = p_alpha_guarded<R>(rR, ph);
-        } else {
-          p_alpha_sound_guarded<R>(rL, ph, paL, aL);
-          p_alpha_sound_guarded<R>(rR, ph, paR, aR);
-        }
-        const R irL = R(1) / uL[0], irR = R(1) / uR[0];
-        R FL[NV], FR[NV], Fc[NV];
-        conv_flux<DIM, R, NV>(d, uL, irL, paL, FL);
-        conv_flux<DIM, R, NV>(d, uR, irR, paR, FR);
-        if constexpr (FLUX == 2) {
-          // global Lax-Friedrichs: one dissipation speed for the whole grid
-#pragma unroll
-          for (int v = 0; v < NV; ++v) Fc[v] = R(0.5) * (FL[v] + FR[v]) - R(0.5) * lam_g * (uR[v] - uL[v]);
-        } else if constexpr (FLUX == 0) {
-          // Rusanov: central flux minus the larger wave speed times the jump
-          const R sL = fabs(uL[1 + d] * irL) + aL;
-          const R sR = fabs(uR[1 + d] * irR) + aR;
-          const R lam = sL > sR ? sL : sR;
-#pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            const R diss = (v == NV - 1 && !ph.diss_c) ? R(0) : lam * (uR[v] - uL[v]);
-            Fc[v] = R(0.5) * (FL[v] + FR[v]) - R(0.5) * diss;
-          }
-        } else {
-          // HLLC of the barotropic convective part: Davis speeds; HLL flux for
-          // mass and normal momentum; tangential momenta carried by the mass
-          // flux with the velocity of the upwind side of the contact
-          // S* = F_hll[rho] / rho_hll; HLL dissipation alone on c
-          const R vnL = uL[1 + d] * irL, vnR = uR[1 + d] * irR;
-          const R SL = fmin(vnL - aL, vnR - aR), SR = fmax(vnL + aL, vnR + aR);
-          if (SL >= R(0)) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) Fc[v] = FL[v];
-          } else if (SR <= R(0)) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) Fc[v] = FR[v];
-          } else {
-            const R w = R(1) / (SR - SL);
-            const R Fm = (SR * FL[0] - SL * FR[0] + SL * SR * (uR[0] - uL[0])) * w;
-            const R rh = (SR * uR[0] - SL * uL[0] - (FR[0] - FL[0])) * w;
-            const bool left = Fm / rh >= R(0);
-            Fc[0] = Fm;
-#pragma unroll
-            for (int j = 0; j < DIM; ++j) {
-              if (j == d)
-                Fc[1 + j] = (SR * FL[1 + j] - SL * FR[1 + j] + SL * SR * (uR[1 + j] - uL[1 + j])) * w;
-              else
-                Fc[1 + j] = Fm * (left ? uL[1 + j] * irL : uR[1 + j] * irR);
-            }
-            Fc[NV - 1] = ph.diss_c ? SL * SR * (uR[NV - 1] - uL[NV - 1]) * w : R(0);
-          }
-        }
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          R Fs = Fc[v];
-          if (v >= 1 && v <= DIM) Fs -= R(0.5) * (vL[v - 1] + vR[v - 1]);
-          if constexpr (MODEL == 0) {
-            if (v == NV - 1) Fs -= R(0.5) * kb * (vL[DIM] + vR[DIM]);
-          }
-          sFs[le][s][v][f] = Fs;
-        }
-      }
-    }
-  };
-  auto accum = [&](auto dc) {
-    constexpr int d = decltype(dc)::value;
-    if (active) {
-      const int sd = dstride<NP>(d);
-      const int i = (n / sd) % NP;
-      const int f = face_of<NP>(d, n);
-      const R h2 = R(info.h2[el][d]);
-      R Drow[NP];
-#pragma unroll
-      for (int l = 0; l < NP; ++l) Drow[l] = sD[i][l];
-      const R lp = sLp[i] * sIw[i], lm = sLm[i] * sIw[i];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        R vol = R(0);
-#pragma unroll
-        for (int l = 0; l < NP; ++l) vol += Drow[l] * sF[PIPE ? (d & 1) : 0][el][v][n + (l - i) * sd];
-        acc[v] += h2 * (vol - (lp * sFs[el][1][v][f] - lm * sFs[el][0][v][f]));
-      }
-    }
-  };
-  stage(std::integral_constant<int, 0>{});
-  __syncthreads();
-  static_for<DIM>([&](auto dc) {
-    constexpr int d = decltype(dc)::value;
-    faces(dc);
-    __syncthreads();
-    accum(dc);
-    if constexpr (d + 1 < DIM) {
-      if constexpr (!PIPE) __syncthreads();  // the single nodal-flux buffer is reused
-      stage(std::integral_constant<int, d + 1>{});
-      __syncthreads();
-    }
-  });
-
-  // source (FP64) and update
-  if (active) {
-    double Rv[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Rv[v] = double(acc[v]);
-    if constexpr (MODEL == 0) {
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) Rv[1 + d] += ph.alpha * rho64 * double(g[NT + d]);
-      Rv[DIM + 1] += ph.ab * (rho64 - c64);
-    }
-    if constexpr (MODEL == 0) {
-      if (st.closure) {
-#pragma unroll
-        for (int d = 0; d <= DIM; ++d) Rv[1 + d] += double(st.closure[d * S + o]);
-      }
-    }
-    if (st.mode == 0) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Uout[v * S + o] = Rv[v];
-    } else {
-#pragma unroll
-      for (int v = 0; v < NV; ++v)
-        if (MIXED) du_old[v] = st.A != 0.0 ? dU[v * S + o] : 0.0;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const double du = st.A * du_old[v] + st.dt * Rv[v];
-        dU[v * S + o] = du;
-        Uout[v * S + o] = u64[v] + st.B * du;
-      }
-    }
-  }
+  if constexpr (DIM == 1)
+    rhs_block_1d<NP, EPB, R, GT, FLUX, MODEL>(L, tid, U, G, Uout, dU, bas, msh, ph, st);
+  else
+    rhs_block_lines<DIM, NP, EPB, R, GT, FLUX, MODEL>(L, tid, U, G, Uout, dU, bas, msh, ph, st);
 }
 
 // -------------------------------------------------------------------------
@@ -847,10 +1234,15 @@ lift_kernel(const double* __restrict__ U, GT* __restrict__ G, BasisArgs bas, Mes
   lift_block<DIM, NP, EPB, R, GT>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, bas, msh, ph);
 }
 
-// The original NSK path's kernel is held to 3 waves per SIMD (it fits in
-// 168 VGPRs without its prefetch); the others keep the compiler's choice.
+// The right-hand-side kernels are held to 3 waves per SIMD (168 VGPRs), where
+// they need no scratch: the degree 4 kernel in 3D FP64 takes 2.41 ms at 2 waves
+// and 2.14 ms at 3 (96x48x48 elements), and scratch costs more than it gains, each
+// spilled register of a thread being written to memory (32 bytes a lane: 2.31 ms).
+// The degree 5 kernel in 3D FP64 would spill and runs at 2.
+template <int DIM, int NP, typename R>
+constexpr int kRhsWaves = DIM == 3 && NP == 6 && sizeof(R) == 8 ? 2 : 3;
 template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX = 0, int MODEL = 0>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(MODEL == 1 ? 3 : 2)))
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves<DIM, NP, R>)))
 rhs_kernel(const double* __restrict__ U, const GT* __restrict__ G, double* __restrict__ Uout,
            double* __restrict__ dU, BasisArgs bas, MeshArgs msh, PhysArgs ph, StageArgs st) {
   rhs_block<DIM, NP, EPB, R, GT, FLUX, MODEL>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, Uout,
@@ -957,7 +1349,7 @@ lift_kernel_batch1(const BatchInst* __restrict__ inst, const BatchItem* __restri
 }
 
 template <int DIM, int NP, int EPB, typename R, typename GT>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves<3, NP, R>)))
 rhs_kernel_batch1(const BatchInst* __restrict__ inst, const BatchItem* __restrict__ items, BasisArgs bas,
                   PhysArgs ph, StageArgs st) {
   const BatchItem w = items[remap_block(blockIdx.x, gridDim.x, kBatchXcds)];
@@ -993,7 +1385,7 @@ lift_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restric
 }
 
 template <int DIM, int NP, int EPB, typename R, typename GT>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves<3, NP, R>)))
 rhs_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restrict__ items, int nitems,
                  BasisArgs bas, PhysArgs ph, StageArgs st) {
   const int slot = remap_block(blockIdx.x, gridDim.x, kBatchXcds);

@@ -256,10 +256,21 @@ BasisArgs basis_args(const nsk_ctx* c) {
   BasisArgs b;
   std::memset(&b, 0, sizeof(b));
   for (int i = 0; i < c->np; ++i) {
-    for (int j = 0; j < c->np; ++j) b.Dhat[i][j] = c->basis.Dhat[i][j];
-    b.Lm[i] = c->basis.Lm[i];
-    b.Lp[i] = c->basis.Lp[i];
-    b.invw[i] = 1.0 / c->basis.w[i];
+    for (int j = 0; j < c->np; ++j) b.d.Dhat[i][j] = c->basis.Dhat[i][j];
+    b.d.Lm[i] = c->basis.Lm[i];
+    b.d.Lp[i] = c->basis.Lp[i];
+    b.d.invw[i] = 1.0 / c->basis.w[i];
+    b.d.wp[i] = b.d.Lp[i] * b.d.invw[i];
+    b.d.wm[i] = b.d.Lm[i] * b.d.invw[i];
+  }
+  // rounded once each, as the FP32 kernels would round them
+  for (int i = 0; i < c->np; ++i) {
+    for (int j = 0; j < c->np; ++j) b.f.Dhat[i][j] = float(b.d.Dhat[i][j]);
+    b.f.Lm[i] = float(b.d.Lm[i]);
+    b.f.Lp[i] = float(b.d.Lp[i]);
+    b.f.invw[i] = float(b.d.invw[i]);
+    b.f.wp[i] = b.f.Lp[i] * b.f.invw[i];
+    b.f.wm[i] = b.f.Lm[i] * b.f.invw[i];
   }
   return b;
 }
@@ -296,19 +307,21 @@ PhysArgs phys_args(const nsk_ctx* c) {
   return p;
 }
 
-// Elements per workgroup: variant 0 is the largest count up to about 256
-// threads whose right-hand-side LDS (FP64) stays within 40 KB; variant 1 is
-// half of it (at least one).
+// Elements per workgroup: variant 0 is the largest count whose lines of one
+// direction fit one wave and whose node pairs fit the waves of all directions
+// (in 1D: 256 nodes); variant 1 is half of it in 1D, where it makes two
+// workgroups of a mesh that one holds, and up to degree 2, where it makes twice
+// the workgroups of a small mesh.  From degree 3 in 2D and 3D it is the same as
+// variant 0: half the lanes of every wave would idle in the line role (1.58
+// against 0.95 ms a stage at N = 4, 64x32x32 elements).
 template <int DIM, int NP>
 struct Epb {
   using Sh = Shape<DIM, NP>;
-  static constexpr int NX = Sh::NVAR + DIM + 1;
-  static constexpr int lds(int epb) {
-    return 8 * epb * (3 * NX * Sh::NN + Sh::NVAR * Sh::NN + 2 * Sh::NVAR * Sh::NF) + 1024;
-  }
-  static constexpr int pick(int epb) { return (epb <= 1 || lds(epb) <= 40960) ? (epb < 1 ? 1 : epb) : pick(epb - 1); }
-  static constexpr int V0 = pick(256 / Sh::NN);
-  static constexpr int V1 = V0 / 2 < 1 ? 1 : V0 / 2;
+  static constexpr int by_pairs = 64 * DIM / ((Sh::NN + 1) / 2);
+  static constexpr int by_lines = 64 / Sh::NF;
+  static constexpr int pick = DIM == 1 ? 256 / Sh::NN : (by_pairs < by_lines ? by_pairs : by_lines);
+  static constexpr int V0 = pick < 1 ? 1 : pick;
+  static constexpr int V1 = (DIM > 1 && NP > 3) || V0 / 2 < 1 ? V0 : V0 / 2;
 };
 
 }  // namespace

@@ -403,16 +403,16 @@ __device__ __forceinline__ void dg_face(const double* U, const double* G, const 
     const int node = base + l * sd;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      uL[v] += bas.Lp[l] * U[v * m.S + oL + node];
-      uR[v] += bas.Lm[l] * U[v * m.S + oR + node];
+      uL[v] += bas.d.Lp[l] * U[v * m.S + oL + node];
+      uR[v] += bas.d.Lm[l] * U[v * m.S + oR + node];
     }
 #pragma unroll
     for (int j = 0; j < DIM; ++j) {
-      vL[j] += bas.Lp[l] * G[(long long)tau_index<DIM>(j, d) * m.S + oL + node];
-      vR[j] += bas.Lm[l] * G[(long long)tau_index<DIM>(j, d) * m.S + oR + node];
+      vL[j] += bas.d.Lp[l] * G[(long long)tau_index<DIM>(j, d) * m.S + oL + node];
+      vR[j] += bas.d.Lm[l] * G[(long long)tau_index<DIM>(j, d) * m.S + oR + node];
     }
-    vL[DIM] += bas.Lp[l] * G[(long long)(NT + d) * m.S + oL + node];
-    vR[DIM] += bas.Lm[l] * G[(long long)(NT + d) * m.S + oR + node];
+    vL[DIM] += bas.d.Lp[l] * G[(long long)(NT + d) * m.S + oL + node];
+    vR[DIM] += bas.d.Lm[l] * G[(long long)(NT + d) * m.S + oR + node];
   }
   conv_numflux<DIM, FLUX>(d, uL, uR, ph, F);
 #pragma unroll
