@@ -296,16 +296,21 @@ __device__ __forceinline__ void mlp_wave(const float4* sX, const uint16_t* sW, c
   }
 }
 
+// 16 bytes of parameters at any address a uint16_t may have (inference wants
+// its parameters 16-byte aligned, training does not).
+struct __attribute__((packed, aligned(2))) ParamWord16 {
+  uint32_t x, y, z, w;
+};
+
 // Stage the parameters the network reads from LDS: W2, W3 as BF16 with
 // padded rows, and W1, b1, b2, b3, W4, b4 as FP32 in the compact block.
-// W2 and W3 move 8 values (16 bytes) per load; w is 16-byte aligned and both
-// blocks start at multiples of 8 values.
+// W2 and W3 move 8 values (16 bytes) per load.
 __device__ __forceinline__ void mlp_stage_params(const uint16_t* __restrict__ w, uint16_t* sW, float* sP) {
   static_assert(kOffW2 % 8 == 0 && kOffW3 % 8 == 0 && kMlpHid % 8 == 0 && kWPad % 4 == 0, "staging layout");
   constexpr int CH = kMlpHid / 8;  // 16-byte chunks per row
   for (int k = threadIdx.x; k < 2 * kMlpHid * CH; k += blockDim.x) {
     const int l = k / (kMlpHid * CH), r = (k / CH) % kMlpHid, cc = k % CH;
-    const uint4 v = *reinterpret_cast<const uint4*>(w + (l ? kOffW3 : kOffW2) + r * kMlpHid + 8 * cc);
+    const ParamWord16 v = *reinterpret_cast<const ParamWord16*>(w + (l ? kOffW3 : kOffW2) + r * kMlpHid + 8 * cc);
     uint2* dst = reinterpret_cast<uint2*>(sW + l * kMlpHid * kWPad + r * kWPad + 8 * cc);
     dst[0] = make_uint2(v.x, v.y);
     dst[1] = make_uint2(v.z, v.w);
