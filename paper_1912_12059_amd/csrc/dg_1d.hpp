@@ -282,4 +282,191 @@ __device__ __forceinline__ void rhs_block_1d(int L, int tid, const double* __res
   }
 }
 
+// -------------------------------------------------------------------------
+// Whole Runge-Kutta steps in one launch (model II).  A workgroup holds up to
+// LE elements, a thread per node, and keeps their state and register in
+// vector registers over the five stages of a step; LDS carries what
+// neighbouring threads read.  An element's stage depends on the two elements
+// on either side, so a mesh of more than LE elements is cut into ranges that
+// overlap by kHalo1D = 10 elements at each end: the values at the ends of a
+// workgroup's range are wrong, two elements deeper with every stage, and only
+// the inner ones are written, one step a launch.  A mesh that fits runs all its
+// steps in one launch, periodic inside the workgroup.
+//
+// The operations on a value and their order are those of the stage kernels,
+// so the bits are the same.  What goes is the launches, two a stage, and the
+// memory round trips: 64 elements, N = 3, FP64: 1.3 us a stage, 3.1 us with the
+// stage kernels' work run in one workgroup through memory; 900 elements: 2.5
+// us, 7.2 us as two launches a stage.  Bound by the chain of one stage: four
+// barriers, and one lane's line sums between them.
+// -------------------------------------------------------------------------
+constexpr int kSteps1DThreads = 512;
+constexpr int kHalo1D = 10;
+template <int NP>
+constexpr int kSteps1DElems = kSteps1DThreads / NP;
+
+struct RkCoefs {
+  double A[5], B[5];
+};
+
+// U1 <- nsteps steps from U0 (a single workgroup may have both the same: a
+// thread reads and writes only its own node).  local: elements of a workgroup; halo: 0 (one
+// workgroup, the whole mesh) or kHalo1D (nsteps = 1).
+template <int NP, typename R, int FLUX>
+__global__ void __launch_bounds__(kSteps1DThreads)
+steps_kernel_1d(const double* U0, double* U1, double* dU, BasisArgs bas, MeshArgs msh, PhysArgs ph,
+                RkCoefs rk, double dt, int nsteps, int local, int halo) {
+  constexpr bool MIXED = sizeof(R) != sizeof(double);
+  constexpr int T = kSteps1DThreads, LE = kSteps1DElems<NP>;
+  __shared__ R sU[3][T], sW[2][T], sG[2][T], sF[3][T];
+  __shared__ double sRho64[MIXED ? T : 1];
+  __shared__ R sWs[2][LE + 1], sFs[3][LE + 1];  // face f: between local elements f - 1 and f
+  __shared__ R sD[NP][NP], sL[5][NP];
+  const auto& B = bas.of(R());
+  const int tid = threadIdx.x, k = tid / NP, i = tid - k * NP;
+  if (tid < NP * NP) sD[tid / NP][tid % NP] = B.Dhat[tid / NP][tid % NP];
+  if (tid < NP) {
+    sL[0][tid] = B.Lm[tid];
+    sL[1][tid] = B.Lp[tid];
+    sL[2][tid] = B.invw[tid];
+    sL[3][tid] = B.wm[tid];
+    sL[4][tid] = B.wp[tid];
+  }
+  const int E = msh.E, own = local - 2 * halo, first = (int)blockIdx.x * own;
+  const bool node = k < local;
+  int e = first + k - halo;
+  if (e < 0) e += E;
+  if (e >= E) e -= E;
+  // the last range may reach round past its own start
+  e = node ? e % E : 0;
+  const long long S = msh.S, o = (long long)e * NP + i;
+  double u[3] = {1.0, 0.0, 1.0}, du[3] = {0.0, 0.0, 0.0};
+  R h2 = R(0);
+  if (node) {
+#pragma unroll
+    for (int v = 0; v < 3; ++v) u[v] = U0[v * S + o];
+    h2 = R(msh.h2[0][e]);
+  }
+  __syncthreads();
+  R D[NP];
+#pragma unroll
+  for (int l = 0; l < NP; ++l) D[l] = sD[i][l];
+  const R Lm = sL[0][i], Lp = sL[1][i], iw = sL[2][i], wm = sL[3][i], wp = sL[4][i];
+  const R kb = R(ph.kb), eps = R(ph.eps);
+  const bool face = tid < local;              // face tid, the left one of element tid
+  const int le = tid == 0 ? local - 1 : tid - 1;  // the element before it
+  const int fr = k + 1 < local ? k + 1 : 0;   // the element's right face
+  const int line = k * NP;
+
+  for (int step = 0; step < nsteps; ++step) {
+    du[0] = du[1] = du[2] = 0.0;
+#pragma nounroll
+    for (int s = 0; s < 5; ++s) {
+      if (node) {
+        const double irho = 1.0 / u[0];
+        sW[0][tid] = R(u[1] * irho);
+        sW[1][tid] = R(u[2]);
+#pragma unroll
+        for (int v = 0; v < 3; ++v) sU[v][tid] = R(u[v]);
+        if (MIXED) sRho64[MIXED ? tid : 0] = u[0];
+      }
+      __syncthreads();
+      if (face) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          R wl = R(0), wr = R(0);
+#pragma unroll
+          for (int l = 0; l < NP; ++l) {
+            wl += B.Lp[l] * sW[c][le * NP + l];
+            wr += B.Lm[l] * sW[c][tid * NP + l];
+          }
+          sWs[c][tid] = R(0.5) * (wl + wr);
+        }
+      }
+      __syncthreads();
+      R gc = R(0);
+      if (node) {
+        R qd[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          R vol = R(0);
+#pragma unroll
+          for (int l = 0; l < NP; ++l) vol += D[l] * sW[c][line + l];
+          const R surf = (Lp * sWs[c][fr] - Lm * sWs[c][k]) * iw;
+          qd[c] = h2 * (surf - vol);
+        }
+        R div = R(0);
+        div += qd[0];
+        R t = eps * (qd[0] + qd[0]);
+        t -= eps * R(2.0 / 3.0) * div;
+        gc = qd[1];
+        sG[0][tid] = t;
+        sG[1][tid] = gc;
+        R ur[3], Fn[3];
+#pragma unroll
+        for (int v = 0; v < 3; ++v) ur[v] = R(u[v]);
+        conv_flux<1, R, 3>(0, ur, R(1) / ur[0], p_alpha_guarded<R>(u[0], ph), Fn);
+        Fn[1] -= t;
+        Fn[2] -= kb * gc;
+#pragma unroll
+        for (int v = 0; v < 3; ++v) sF[v][tid] = Fn[v];
+      }
+      __syncthreads();
+      if (face) {
+        R uL[3], uR[3], vL[2], vR[2], Fs[3];
+        double rL = 0.0, rR = 0.0;
+#pragma unroll
+        for (int v = 0; v < 3; ++v) uL[v] = uR[v] = R(0);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) vL[c] = vR[c] = R(0);
+#pragma unroll
+        for (int l = 0; l < NP; ++l) {
+          const int a = le * NP + l, b = tid * NP + l;
+          rL += bas.d.Lp[l] * (MIXED ? sRho64[MIXED ? a : 0] : double(sU[0][a]));
+          rR += bas.d.Lm[l] * (MIXED ? sRho64[MIXED ? b : 0] : double(sU[0][b]));
+#pragma unroll
+          for (int v = 0; v < 3; ++v) {
+            uL[v] += B.Lp[l] * sU[v][a];
+            uR[v] += B.Lm[l] * sU[v][b];
+          }
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            vL[c] += B.Lp[l] * sG[c][a];
+            vR[c] += B.Lm[l] * sG[c][b];
+          }
+        }
+        face_flux<1, R, FLUX, 0, 0, 3, 2>(uL, uR, vL, vR, rL, rR, R(0), kb, ph, Fs);
+#pragma unroll
+        for (int v = 0; v < 3; ++v) sFs[v][tid] = Fs[v];
+      }
+      __syncthreads();
+      if (node) {
+        double Rv[3];
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+          R vol = R(0), acc = R(0);
+#pragma unroll
+          for (int l = 0; l < NP; ++l) vol += D[l] * sF[v][line + l];
+          acc += h2 * (vol - (wp * sFs[v][fr] - wm * sFs[v][k]));
+          Rv[v] = double(acc);
+        }
+        Rv[1] += ph.alpha * u[0] * double(gc);
+        Rv[2] += ph.ab * (u[0] - u[2]);
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+          du[v] = rk.A[s] * du[v] + dt * Rv[v];
+          u[v] = u[v] + rk.B[s] * du[v];
+        }
+      }
+    }
+  }
+  if (node && k >= halo && k < local - halo && first + k - halo < E) {
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+      U1[v * S + o] = u[v];
+      dU[v * S + o] = du[v];
+    }
+  }
+}
+
 }  // namespace nsk

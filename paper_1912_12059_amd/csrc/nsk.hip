@@ -289,36 +289,44 @@ bool variants_coincide(int dim, int N) {
   return dim == 1 ? variants_coincide_dim<1>(N) : dim == 2 ? variants_coincide_dim<2>(N) : variants_coincide_dim<3>(N);
 }
 
-// Whole steps in one launch of one workgroup: 1D model II meshes (FP64 or
-// mixed, Rusanov or HLLC, no closure, no sub-cells) that the first tile
-// variant holds in one workgroup, unless per-stage timing is on.
-template <int NP, typename R, typename GT>
+// Whole steps in one launch: 1D model II (FP64 or mixed, Rusanov or HLLC, no
+// closure, no sub-cells) with the first tile variant, unless per-stage timing
+// is on.  A mesh that a workgroup holds runs nsteps steps, a larger one a step
+// (the caller launches nsteps = 1 at a time).  The state's buffer alternates
+// with every step, as five stages would leave it.
+int elems_in_one_workgroup(const nsk_ctx* c) { return kSteps1DThreads / c->np; }
+
+template <int NP, typename R>
 int launch_steps_t(nsk_ctx* c, double dt, int nsteps) {
-  constexpr int EPB = Epb<1, NP>::V0;
-  using Tl = Tile<1, NP, EPB>;
   RkCoefs rk;
   for (int s = 0; s < 5; ++s) {
     rk.A[s] = kRkA[s];
     rk.B[s] = kRkB[s];
   }
-  GT* G = reinterpret_cast<GT*>(c->work + c->off_G);
+  const bool one = c->E <= kSteps1DElems<NP>;
+  const int local = one ? (int)c->E : kSteps1DElems<NP>, halo = one ? 0 : kHalo1D;
+  const int own = local - 2 * halo;
+  const unsigned grid = (unsigned)((c->E + own - 1) / own);
+  const unsigned threads = (unsigned)round64(local * NP);
+  // a single workgroup may write the buffer it starts from
+  const int next = (nsteps & 1) ? 1 - c->cur : c->cur;
+  const auto f = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, c->stream, state_buf(c, c->cur), state_buf(c, next), c->dU,
+                       basis_args(c), mesh_args(c), phys_args(c), rk, dt, nsteps, local, halo);
+  };
   if (c->par.flux == 1)
-    hipLaunchKernelGGL((steps_kernel<1, NP, EPB, R, GT, 1>), dim3(1), dim3(Tl::THREADS), 0, c->stream,
-                       state_buf(c, 0), state_buf(c, 1), G, c->dU, basis_args(c), mesh_args(c), phys_args(c), rk, dt,
-                       nsteps, c->cur);
+    f(steps_kernel_1d<NP, R, 1>);
   else
-    hipLaunchKernelGGL((steps_kernel<1, NP, EPB, R, GT, 0>), dim3(1), dim3(Tl::THREADS), 0, c->stream,
-                       state_buf(c, 0), state_buf(c, 1), G, c->dU, basis_args(c), mesh_args(c), phys_args(c), rk, dt,
-                       nsteps, c->cur);
+    f(steps_kernel_1d<NP, R, 0>);
   if (hipGetLastError() != hipSuccess) return NSK_EHIP;
-  if (nsteps & 1) c->cur = 1 - c->cur;  // five buffer swaps per step
+  c->cur = next;
   return NSK_OK;
 }
 
 template <int NP>
 int launch_steps_np(nsk_ctx* c, double dt, int nsteps) {
-  if (c->par.precision == 0) return launch_steps_t<NP, double, double>(c, dt, nsteps);
-  return launch_steps_t<NP, float, float>(c, dt, nsteps);
+  if (c->par.precision == 0) return launch_steps_t<NP, double>(c, dt, nsteps);
+  return launch_steps_t<NP, float>(c, dt, nsteps);
 }
 
 int launch_steps(nsk_ctx* c, double dt, int nsteps) {
@@ -333,28 +341,23 @@ int launch_steps(nsk_ctx* c, double dt, int nsteps) {
   return NSK_EUNSUPPORTED;
 }
 
-int epb_v0_1d(int np) {
-  switch (np) {
-    case 2: return Epb<1, 2>::V0;
-    case 3: return Epb<1, 3>::V0;
-    case 4: return Epb<1, 4>::V0;
-    case 5: return Epb<1, 5>::V0;
-    case 6: return Epb<1, 6>::V0;
-    case 7: return Epb<1, 7>::V0;
-  }
-  return 0;
+bool whole_steps(const nsk_ctx* c) {
+  return c->dim == 1 && c->par.model == 0 && c->par.subcell == 0 && c->par.closure == 0 && c->events.empty() &&
+         (c->tile == 0 || variants_coincide(1, c->N));
 }
 
-bool steps_in_one_workgroup(const nsk_ctx* c) {
-  if (c->dim != 1 || c->par.model != 0 || c->par.subcell != 0 || c->par.closure != 0 || !c->events.empty())
-    return false;
-  if (c->tile != 0 && !variants_coincide(1, c->N)) return false;
-  return c->E <= epb_v0_1d(c->np);
-}
+bool steps_in_one_workgroup(const nsk_ctx* c) { return whole_steps(c) && c->E <= elems_in_one_workgroup(c); }
 
-// nsteps Runge-Kutta steps enqueued stage by stage on the bound stream
+// nsteps Runge-Kutta steps enqueued on the bound stream, step by step where a
+// launch takes a whole step, else stage by stage
 int enqueue_steps(nsk_ctx* c, double dt, int nsteps) {
+  const bool whole = whole_steps(c);
   for (int step = 0; step < nsteps; ++step) {
+    if (whole) {
+      const int rc = launch_steps(c, dt, 1);
+      if (rc) return rc;
+      continue;
+    }
     for (int s = 0; s < 5; ++s) {
       StageArgs st{kRkA[s], kRkB[s], dt, 1};
       c->cl_stage = s;
