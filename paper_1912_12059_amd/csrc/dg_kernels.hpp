@@ -1379,10 +1379,20 @@ rhs_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restrict
 // -------------------------------------------------------------------------
 constexpr int kDiagSlots = 13;
 
-__device__ __forceinline__ int elem_index_dir_diag(const MeshArgs& m, long long e, int d) {
-  if (d == 0) return int(e % m.nel[0]);
-  if (d == 1) return int((e / m.nel[0]) % m.nel[1]);
-  return int(e / ((long long)m.nel[0] * m.nel[1]));
+// index of element e in each direction (elements are numbered in 32 bits: the
+// work order is a table of ints)
+template <int DIM>
+__device__ __forceinline__ void elem_index_diag(const MeshArgs& m, unsigned e, int (&c)[DIM]) {
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    if (d == DIM - 1) {
+      c[d] = int(e);
+    } else {
+      const unsigned n = unsigned(m.nel[d]), q = e / n;
+      c[d] = int(e - q * n);
+      e = q;
+    }
+  }
 }
 constexpr int kDiagThreads = 256;
 
@@ -1395,68 +1405,170 @@ __device__ __forceinline__ double diag_combine(int k, double a, double b) {
   return k == 8 ? fmin(a, b) : ((k == 9 || k == 10 || k == 12) ? fmax(a, b) : a + b);
 }
 
-template <int DIM, int NP, typename GT, int MODEL = 0>
-__global__ void __launch_bounds__(kDiagThreads)
-diag_partial_kernel(const double* __restrict__ U, const GT* __restrict__ G, double* __restrict__ part,
-                    const double* __restrict__ wq1, MeshArgs msh, PhysArgs ph) {
+// the block's value of every slot, in a fixed order: lanes by shuffles, then the
+// waves; red is free again when it returns (thread 0..kDiagSlots-1 hold a slot)
+__device__ __forceinline__ double diag_block_reduce(double (&acc)[kDiagSlots], double (*red)[kDiagSlots]) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < kDiagSlots; ++k)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc[k] = diag_combine(k, acc[k], __shfl_down(acc[k], off));
+  if ((tid & 63) == 0)
+    for (int k = 0; k < kDiagSlots; ++k) red[tid >> 6][k] = acc[k];
+  __syncthreads();
+  double r = 0.0;
+  if (tid < kDiagSlots) {
+    r = red[0][tid];
+    for (int w = 1; w < kDiagThreads / 64; ++w) r = diag_combine(tid, r, red[w][tid]);
+  }
+  return r;
+}
+
+// One thread per node for the pointwise terms; the lifted gradient of c (of rho
+// in the original NSK path), which the energy needs, is formed here too, one
+// thread per element line, so that the state is read once and no lifted
+// gradients are written (a launch of the lifting kernel, then 72 bytes a node
+// written and 24 read).  R: the precision of the lifting.  FULL false: only what
+// the step size needs (slots 8..12), without gradient, integrals and logarithm.
+// One reciprocal of rho and of the volume a node, element indexes in 32 bits and
+// four workgroups a CU (the grid's 1024 are then resident at once): with the
+// divisions of each term by itself, 64-bit indexes and three workgroups 144 us.
+// Measured at 48x24x24, N = 4, FP64: 107 us, and 43 us without FULL (29 us to
+// read the state at the rate of a large copy); a lifting launch and a kernel that
+// took each element's maxima with one thread were 148 + 151 us for both.
+template <int DIM, int NP, typename R, int MODEL, bool FULL>
+__global__ void __launch_bounds__(kDiagThreads, 4)
+diag_partial_kernel(const double* __restrict__ U, double* __restrict__ part, const double* __restrict__ wq1,
+                    BasisArgs bas, MeshArgs msh, PhysArgs ph) {
   using Sh = Shape<DIM, NP>;
-  constexpr int NN = Sh::NN, NT = Sh::NTAU;
+  constexpr int NN = Sh::NN, NF = Sh::NF;
   constexpr int NV = MODEL == 1 ? DIM + 1 : DIM + 2;
+  constexpr int SI = MODEL == 1 ? 0 : DIM + 1;  // the lifted scalar
   constexpr int EPBD = (kDiagThreads / NN) > 0 ? kDiagThreads / NN : 1;  // whole elements per group
-  constexpr int SLOTS = EPBD * NN;
-  __shared__ double red[kDiagSlots][kDiagThreads];
+  constexpr int SLOTS = EPBD * NN, LINES = EPBD * NF;
+  static_assert(SLOTS <= kDiagThreads, "one thread per node");
+  __shared__ double red[kDiagThreads / 64][kDiagSlots];
   __shared__ double spd[DIM][kDiagThreads];  // per-node |v_d| + a
+  __shared__ R sC[FULL ? SLOTS : 1], sX[DIM][FULL ? SLOTS : 1];
+  const auto& B = bas.of(R());
   const int tid = threadIdx.x;
   double acc[kDiagSlots];
+#pragma unroll
   for (int k = 0; k < kDiagSlots; ++k) acc[k] = 0.0;
   acc[8] = INFINITY;
   acc[9] = -INFINITY;
   const long long S = msh.S;
   const int el = tid / NN, n = tid - (tid / NN) * NN;
-  int r = n;
   double wn = 1.0;  // tensor-product quadrature weight of the node
+  if constexpr (FULL) {
+    int r = n;
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) { wn *= wq1[r % NP]; r /= NP; }
+    for (int d = 0; d < DIM; ++d) { wn *= wq1[r % NP]; r /= NP; }
+  }
   // groups of whole elements, one thread per node (coalesced loads); the
   // per-element directional maxima of the wave speed go through LDS
   const long long ngroups = (msh.E + EPBD - 1) / EPBD;
   for (long long grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
     const long long e = grp * EPBD + el;
     const bool active = tid < SLOTS && e < msh.E;
-    double hinv[DIM];
+    double u[NV];
+    if (active) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) u[v] = U[v * S + e * NN + n];
+    }
+    if constexpr (FULL) {
+      if (active) sC[tid] = R(u[SI]);
+      // the two neighbours' traces of a line, then the line
+      constexpr int ROUNDS = (DIM * LINES + kDiagThreads - 1) / kDiagThreads;
+      R tr[ROUNDS][2];
+      double h2l[ROUNDS];
+#pragma unroll
+      for (int q = 0; q < ROUNDS; ++q) {
+        const int i = tid + q * kDiagThreads, d = i / LINES, le = (i - d * LINES) / NF, f = i % NF;
+        const long long ee = grp * EPBD + le;
+        tr[q][0] = tr[q][1] = R(0);
+        h2l[q] = 0.0;
+        if (d < DIM && ee < msh.E) {
+          int ci[DIM];
+          elem_index_diag<DIM>(msh, unsigned(ee), ci);
+          int c = ci[0], step = 1, nd = msh.nel[0];
+          const double* h2 = msh.h2[0];
+#pragma unroll
+          for (int k = 1; k < DIM; ++k)
+            if (d == k) { c = ci[k]; step = k == 1 ? msh.nel[0] : msh.nel[0] * msh.nel[1]; nd = msh.nel[k]; h2 = msh.h2[k]; }
+          const int sd = dstride<NP>(d), base = face_base<NP>(d, f);
+          h2l[q] = h2[c];
+          const long long nb[2] = {c == 0 ? ee + (long long)(nd - 1) * step : ee - step,
+                                   c == nd - 1 ? ee - (long long)(nd - 1) * step : ee + step};
+          double x[2][NP];
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int l = 0; l < NP; ++l) x[s][l] = U[SI * S + nb[s] * NN + base + l * sd];
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int l = 0; l < NP; ++l) tr[q][s] += (s ? B.Lm[l] : B.Lp[l]) * R(x[s][l]);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < ROUNDS; ++q) {
+        const int i = tid + q * kDiagThreads, d = i / LINES, le = (i - d * LINES) / NF, f = i % NF;
+        if (d < DIM && grp * EPBD + le < msh.E) {
+          const int sd = dstride<NP>(d), b0 = le * NN + face_base<NP>(d, f);
+          R w[NP], wl = R(0), wr = R(0);
+#pragma unroll
+          for (int l = 0; l < NP; ++l) {
+            w[l] = sC[b0 + l * sd];
+            wl += B.Lp[l] * w[l];
+            wr += B.Lm[l] * w[l];
+          }
+          const R wsm = R(0.5) * (tr[q][0] + wr), wsp = R(0.5) * (wl + tr[q][1]), h2 = R(h2l[q]);
+#pragma unroll
+          for (int m = 0; m < NP; ++m) {
+            R vol = R(0);
+#pragma unroll
+            for (int l = 0; l < NP; ++l) vol += B.Dhat[m][l] * w[l];
+            const R surf = (B.Lp[m] * wsp - B.Lm[m] * wsm) * B.invw[m];
+            sX[d][b0 + m * sd] = h2 * (surf - vol);
+          }
+        }
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int d = 0; d < DIM; ++d) spd[d][tid] = 0.0;
     if (active) {
-      const long long o = e * NN + n;
-      double J = 1.0;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        const double h2 = msh.h2[d][elem_index_dir_diag(msh, e, d)];
-        J *= 1.0 / h2;  // h/2
-        hinv[d] = 0.5 * h2;
-      }
-      const double wgt = J * wn;
-      double u[NV];
       bool finite = true;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        u[v] = U[v * S + o];
+      for (int v = 0; v < NV; ++v)
         if (!isfinite(u[v])) { acc[11] += 1.0; finite = false; }
-        acc[v] += wgt * u[v];
-      }
-      // model II: c and its lifted gradient; original NSK: the lifted
-      // gradient of rho in the same slots, no relaxation energy
-      const double rho = u[0], c = MODEL == 0 ? u[NV - 1] : rho;
-      double ek = 0.0, gc2 = 0.0;
+      const double rho = u[0], ir = 1.0 / rho;
+      if constexpr (FULL) {
+        int ci[DIM];
+        elem_index_diag<DIM>(msh, unsigned(e), ci);
+        double hv = 1.0;
 #pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        ek += 0.5 * u[1 + d] * u[1 + d] / rho;
-        const double gcd = double(G[(long long)(NT + d) * S + o]);
-        gc2 += gcd * gcd;
+        for (int d = 0; d < DIM; ++d) hv *= msh.h2[d][ci[d]];
+        const double wgt = wn / hv;  // J = prod of h/2
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] += wgt * u[v];
+        // model II: c and its lifted gradient; original NSK: the lifted
+        // gradient of rho, no relaxation energy
+        const double c = MODEL == 0 ? u[NV - 1] : rho;
+        double m2 = 0.0, gc2 = 0.0;
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+          m2 += u[1 + d] * u[1 + d];
+          const double gcd = double(sX[d][tid]);
+          gc2 += gcd * gcd;
+        }
+        const double ek = 0.5 * m2 * ir;
+        acc[5] += wgt * ek;
+        acc[6] += wgt * (ek + vdw_W(rho, ph.T) + 0.5 * ph.alpha * (rho - c) * (rho - c) + 0.5 * ph.kappa * gc2);
+        acc[7] += wgt * (rho - c) * (rho - c);
       }
-      acc[5] += wgt * ek;
-      acc[6] += wgt * (ek + vdw_W(rho, ph.T) + 0.5 * ph.alpha * (rho - c) * (rho - c) + 0.5 * ph.kappa * gc2);
-      acc[7] += wgt * (rho - c) * (rho - c);
       if (finite) {
         acc[8] = fmin(acc[8], rho);
         acc[9] = fmax(acc[9], rho);
@@ -1469,54 +1581,51 @@ diag_partial_kernel(const double* __restrict__ U, const GT* __restrict__ G, doub
         }
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
-          const double sp = fabs(u[1 + d] / rho) + a;
+          const double sp = fabs(u[1 + d] * ir) + a;
           acc[10] = fmax(acc[10], sp);
           spd[d][tid] = sp;
         }
       }
     }
     __syncthreads();
-    if (active && n == 0) {
+    // max over the element's nodes along each direction, 16 lanes an element;
+    // the maximum does not depend on the order of its operands
+    for (int q = tid / 16; q < EPBD; q += kDiagThreads / 16) {
+      if (grp * EPBD + q >= msh.E) continue;
+      int ci[DIM];
+      elem_index_diag<DIM>(msh, unsigned(grp * EPBD + q), ci);
       double lam = 0.0;
 #pragma unroll
       for (int d = 0; d < DIM; ++d) {
         double m = 0.0;
-        for (int k = 0; k < NN; ++k) m = fmax(m, spd[d][el * NN + k]);
-        lam += m * hinv[d];
+        for (int k = tid % 16; k < NN; k += 16) m = fmax(m, spd[d][q * NN + k]);
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 16));
+        lam += m * (0.5 * msh.h2[d][ci[d]]);
       }
       acc[12] = fmax(acc[12], lam);
     }
     __syncthreads();
   }
-  for (int k = 0; k < kDiagSlots; ++k) red[k][tid] = acc[k];
-  __syncthreads();
-  for (int w = kDiagThreads / 2; w > 0; w >>= 1) {
-    if (tid < w)
-      for (int k = 0; k < kDiagSlots; ++k) red[k][tid] = diag_combine(k, red[k][tid], red[k][tid + w]);
-    __syncthreads();
-  }
-  if (tid < kDiagSlots) part[(long long)blockIdx.x * kDiagSlots + tid] = red[tid][0];
+  const double r = diag_block_reduce(acc, red);
+  if (tid < kDiagSlots) part[(long long)blockIdx.x * kDiagSlots + tid] = r;
 }
 
+// the blocks' partial values, in a fixed order
 template <int SLOTS>
 __global__ void __launch_bounds__(kDiagThreads) diag_final_kernel(const double* __restrict__ part, int nblocks,
                                                                   double* __restrict__ out) {
-  __shared__ double red[kDiagSlots][kDiagThreads];
-  const int tid = threadIdx.x;
+  __shared__ double red[kDiagThreads / 64][kDiagSlots];
   double acc[kDiagSlots];
+#pragma unroll
   for (int k = 0; k < kDiagSlots; ++k) acc[k] = 0.0;
   acc[8] = INFINITY;
   acc[9] = -INFINITY;
-  for (int b = tid; b < nblocks; b += kDiagThreads)
+  for (int b = threadIdx.x; b < nblocks; b += kDiagThreads)
+#pragma unroll
     for (int k = 0; k < kDiagSlots; ++k) acc[k] = diag_combine(k, acc[k], part[(long long)b * kDiagSlots + k]);
-  for (int k = 0; k < kDiagSlots; ++k) red[k][tid] = acc[k];
-  __syncthreads();
-  for (int w = kDiagThreads / 2; w > 0; w >>= 1) {
-    if (tid < w)
-      for (int k = 0; k < kDiagSlots; ++k) red[k][tid] = diag_combine(k, red[k][tid], red[k][tid + w]);
-    __syncthreads();
-  }
-  if (tid < kDiagSlots) out[tid] = red[tid][0];
+  const double r = diag_block_reduce(acc, red);
+  if (threadIdx.x < kDiagSlots) out[threadIdx.x] = r;
 }
 
 }  // namespace nsk

@@ -185,50 +185,38 @@ int launch_stage_t(nsk_ctx* c, const double* Uin, double* Uout, double* dU, cons
   return launch_stage_e<DIM, NP, Epb<DIM, NP>::V0, R, GT>(c, Uin, Uout, dU, st);
 }
 
-template <int DIM, int NP, typename GT>
+template <int DIM, int NP, typename R, bool FULL>
 int launch_diag_t(nsk_ctx* c, const double* Uin) {
-  constexpr int EPB = Epb<DIM, NP>::V0;
-  using Tl = Tile<DIM, NP, EPB>;
   const BasisArgs b = basis_args(c);
   const MeshArgs m = mesh_args(c);
   const PhysArgs p = phys_args(c);
-  GT* G = reinterpret_cast<GT*>(c->work + c->off_G);
-  const unsigned blocks = (unsigned)((c->E + EPB - 1) / EPB);
-  using R = GT;
   double* part = reinterpret_cast<double*>(c->work + c->off_part);
   double* out = reinterpret_cast<double*>(c->work + c->off_out);
   const double* wq = reinterpret_cast<const double*>(c->work + c->off_wq);
+  const dim3 grid(c->diag_blocks), block(kDiagThreads);
   bool done = false;
-  if constexpr (std::is_same<GT, double>::value) {
+  if constexpr (std::is_same<R, double>::value) {
     if (c->par.model == 1) {
-      // the lifted gradient of rho for the capillary energy; the speed is
-      // reduced by the diagnostics kernel itself
-      hipLaunchKernelGGL((nsk_lift_kernel<DIM, NP, EPB>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b, m,
-                         p, nullptr);
-      hipLaunchKernelGGL((diag_partial_kernel<DIM, NP, GT, 1>), dim3(c->diag_blocks), dim3(kDiagThreads), 0,
-                         c->stream, Uin, G, part, wq, m, p);
+      hipLaunchKernelGGL((diag_partial_kernel<DIM, NP, R, 1, FULL>), grid, block, 0, c->stream, Uin, part, wq, b, m, p);
       done = true;
     }
   }
-  if (!done) {
-    hipLaunchKernelGGL((lift_kernel<DIM, NP, EPB, R, GT>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b,
-                       m, p);
-    hipLaunchKernelGGL((diag_partial_kernel<DIM, NP, GT>), dim3(c->diag_blocks), dim3(kDiagThreads), 0, c->stream,
-                       Uin, G, part, wq, m, p);
-  }
-  hipLaunchKernelGGL(diag_final_kernel<kDiagSlots>, dim3(1), dim3(kDiagThreads), 0, c->stream, part, c->diag_blocks,
-                     out);
+  if (!done)
+    hipLaunchKernelGGL((diag_partial_kernel<DIM, NP, R, 0, FULL>), grid, block, 0, c->stream, Uin, part, wq, b, m, p);
+  hipLaunchKernelGGL(diag_final_kernel<kDiagSlots>, dim3(1), block, 0, c->stream, part, c->diag_blocks, out);
   return hipGetLastError() == hipSuccess ? NSK_OK : NSK_EHIP;
 }
 
 template <int DIM, int NP>
 int dispatch_prec(nsk_ctx* c, int what, const double* Uin, double* Uout, double* dU, const StageArgs& st) {
+  // the step size takes no gradient: one FP64 kernel for both precisions
+  if (what == 2) return launch_diag_t<DIM, NP, double, false>(c, Uin);
   if (c->par.precision == 0) {
     if (what == 0) return launch_stage_t<DIM, NP, double, double>(c, Uin, Uout, dU, st);
-    return launch_diag_t<DIM, NP, double>(c, Uin);
+    return launch_diag_t<DIM, NP, double, true>(c, Uin);
   }
   if (what == 0) return launch_stage_t<DIM, NP, float, float>(c, Uin, Uout, dU, st);
-  return launch_diag_t<DIM, NP, float>(c, Uin);
+  return launch_diag_t<DIM, NP, float, true>(c, Uin);
 }
 
 template <int DIM>
@@ -246,7 +234,7 @@ int dispatch_np(nsk_ctx* c, int what, const double* Uin, double* Uout, double* d
   return NSK_EUNSUPPORTED;
 }
 
-// what = 0: one stage (lift + rhs), what = 1: diagnostics
+// what = 0: one stage (lift + rhs), 1: diagnostics, 2: what the step size needs of them
 int dispatch(nsk_ctx* c, int what, const double* Uin, double* Uout, double* dU, const StageArgs& st) {
   switch (c->dim) {
     case 1: return dispatch_np<1>(c, what, Uin, Uout, dU, st);
@@ -260,9 +248,9 @@ double* state_buf(nsk_ctx* c, int which) {
   return which == 0 ? c->U : reinterpret_cast<double*>(c->work + c->off_U2);
 }
 
-int run_diag(nsk_ctx* c, double* h) {
+int run_diag(nsk_ctx* c, int what, double* h) {
   StageArgs st{0.0, 0.0, 0.0, 0};
-  int rc = dispatch(c, 1, state_buf(c, c->cur), nullptr, nullptr, st);
+  int rc = dispatch(c, what, state_buf(c, c->cur), nullptr, nullptr, st);
   if (rc) return rc;
   if (hipMemcpyAsync(h, c->work + c->off_out, sizeof(double) * kDiagSlots, hipMemcpyDeviceToHost, c->stream) !=
       hipSuccess)
@@ -813,7 +801,7 @@ int nsk_diagnostics(nsk_ctx* c, nsk_diag* o) {
   if (!c || !o) return NSK_EINVAL;
   if (!c->bound) return NSK_EUNBOUND;
   double h[kDiagSlots];
-  int rc = run_diag(c, h);
+  int rc = run_diag(c, 1, h);
   if (rc) return rc;
   std::memset(o, 0, sizeof(*o));
   for (int v = 0; v < c->nvar; ++v) o->mass[v] = h[v];
@@ -833,7 +821,7 @@ int nsk_dt_estimate(nsk_ctx* c, double cfl, double* dt_out) {
   if (!c || !dt_out || !(cfl > 0.0)) return NSK_EINVAL;
   if (!c->bound) return NSK_EUNBOUND;
   double h[kDiagSlots];
-  int rc = run_diag(c, h);
+  int rc = run_diag(c, 2, h);
   if (rc) return rc;
   if (h[11] > 0.0 || !(h[8] > 0.0)) return NSK_ENONPHYS;
   const double N2 = 2.0 * c->N + 1.0;
