@@ -173,6 +173,10 @@ struct nsk_ctx {
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   std::vector<unsigned char> graph_key;
+  // implicit steps: what the host reads of a reduction (pinned, a few hundred
+  // bytes) and the event that says it is written; from the first such call on
+  double* sync_host = nullptr;
+  hipEvent_t sync_event = nullptr;
 };
 
 namespace {

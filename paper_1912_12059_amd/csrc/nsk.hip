@@ -612,6 +612,8 @@ void nsk_destroy(nsk_ctx* c) {
   if (c->bound) (void)hipStreamSynchronize(c->stream);
   drop_step_graph(c);
   for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
+  if (c->sync_event) (void)hipEventDestroy(c->sync_event);
+  if (c->sync_host) (void)hipHostFree(c->sync_host);
   delete c;
 }
 
