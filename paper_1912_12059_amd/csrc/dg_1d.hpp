@@ -245,7 +245,9 @@ __device__ __forceinline__ void rhs_block_1d(int L, int tid, const double* __res
         vR[c] += B.Lm[l] * sX[s + 1][NV + c][a];
       }
     }
-    face_flux<1, R, FLUX, MODEL, 0, NV, NVX>(uL, uR, vL, vR, rL, rR, lam_g, kb, ph, Fs);
+#pragma unroll
+    for (int c = 0; c < NVX; ++c) vL[c] += vR[c];
+    face_flux<1, R, FLUX, MODEL, 0, NV, NVX>(uL, uR, vL, rL, rR, lam_g, kb, ph, Fs);
 #pragma unroll
     for (int v = 0; v < NV; ++v) sFs[s][v][q] = Fs[v];
   }
@@ -435,7 +437,9 @@ steps_kernel_1d(const double* U0, double* U1, double* dU, BasisArgs bas, MeshArg
             vR[c] += B.Lm[l] * sG[c][b];
           }
         }
-        face_flux<1, R, FLUX, 0, 0, 3, 2>(uL, uR, vL, vR, rL, rR, R(0), kb, ph, Fs);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) vL[c] += vR[c];
+        face_flux<1, R, FLUX, 0, 0, 3, 2>(uL, uR, vL, rL, rR, R(0), kb, ph, Fs);
 #pragma unroll
         for (int v = 0; v < 3; ++v) sFs[v][tid] = Fs[v];
       }
