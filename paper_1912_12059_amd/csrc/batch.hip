@@ -85,6 +85,13 @@ void drop_graph(nsk_batch* b) {
   b->graph_dt = -1.0;
 }
 
+// what the stages stream past the caches: all instances take a stage together
+int batch_stream(const nsk_batch* b) {
+  double t = 0.0;
+  for (int i = 0; i < b->ninst; ++i) t += stage_bytes(b->ctx[i]);
+  return stream_bits(t);
+}
+
 // descriptor of instance i for stage parity p: p = 0 reads U, writes the
 // workspace copy; p = 1 the reverse
 BatchInst make_desc(nsk_batch* b, int i, int p) {
@@ -97,6 +104,7 @@ BatchInst make_desc(nsk_batch* b, int i, int p) {
   d.G = c->work + c->off_G;
   d.msh = mesh_args(c);
   d.msh.nxcd = 1;
+  d.msh.stream = batch_stream(b);
   return d;
 }
 
@@ -191,7 +199,8 @@ int launch_single_e(nsk_batch* b, nsk_ctx* c, int parity, const StageArgs& st) {
   double* Uout = parity ? c->U : U2;
   GT* G = reinterpret_cast<GT*>(c->work + c->off_G);
   const BasisArgs bas = basis_args(c);
-  const MeshArgs m = mesh_args(c);
+  MeshArgs m = mesh_args(c);
+  m.stream = batch_stream(b);
   const PhysArgs ph = phys_args(c);
   const unsigned blocks = (unsigned)((c->E + EPB - 1) / EPB);
   hipLaunchKernelGGL((lift_kernel<3, NP, EPB, R, GT>), dim3(blocks), dim3(Tl::THREADS), 0, b->stream, Uin, G, bas, m,

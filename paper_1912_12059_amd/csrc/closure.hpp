@@ -20,9 +20,10 @@
 // accumulator layout of one layer is the B-operand layout of the next), and
 // layer 4 as an FP32 dot product finished across the two half-waves.
 //
-// Training runs in FP32 vector arithmetic with the same rounding points
-// (BF16 parameters; BF16 activations where inference feeds a BF16 MFMA), so the
-// trained network is the one inference evaluates up to summation order.
+// Training (mlp_train_kernel) keeps the same rounding points (BF16 parameters;
+// BF16 activations where inference feeds a BF16 MFMA), so the trained network is
+// the one inference evaluates up to summation order; its products run on the
+// matrix cores with FP32 accumulation, FP32 operands as sums of three BF16.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

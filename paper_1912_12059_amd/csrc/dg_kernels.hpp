@@ -98,7 +98,22 @@ struct MeshArgs {
   int E;                // number of elements
   long long S;          // E * NN, stride between variables
   int nxcd;             // XCDs sharing the work order in contiguous ranges
+  int stream;           // kStreamState, kStreamG: arrays that pass the caches by
 };
+
+// Arrays that the next kernel will not find in the last-level cache (256 MB) are
+// written without a place in it (and the old dU read so), which leaves the caches
+// to the neighbours' lines.  The lines lie, by the bytes of the two states, dU and
+// G together, where both sides are equal: ms a stage without / with, 3D N = 4 FP64
+// 0.114 / 0.121 at 197 MB, 0.232 / 0.214 at 384 MB, N = 2 0.111 / 0.128 at 228 MB,
+// mixed 0.181 / 0.174 at 312 MB, 2D N = 4 0.120 / 0.129 at 267 MB.  G in FP64 from a
+// larger size on, as the next kernel reads it at once: 0.214 / 0.221 at 384 MB (state
+// and dU streamed in both), 0.378 / 0.367 at 664 MB; in FP32 it is left alone.
+constexpr int kStreamState = 1, kStreamG = 2;
+constexpr double kStreamStateBytes = 288e6, kStreamGBytes = 512e6;
+inline int stream_bits(double bytes) {
+  return (bytes > kStreamStateBytes ? kStreamState : 0) | (bytes > kStreamGBytes ? kStreamG : 0);
+}
 
 struct PhysArgs {
   double T, eps, kappa, alpha, beta;
@@ -253,8 +268,8 @@ __device__ __forceinline__ void block_max_store(double v, double* red, double* o
 // change nothing.
 //
 // Measured, ms a launch, one direction after the other / this form:
-//   3D N = 4, 96x48x48, FP64    lift 1.19 / 1.11   rhs 2.55 / 1.96
-//   3D N = 4, 96x48x48, mixed   lift 0.85 / 0.78   rhs 1.82 / 1.75
+//   3D N = 4, 96x48x48, FP64    lift 1.19 / 1.05   rhs 2.55 / 1.90
+//   3D N = 4, 96x48x48, mixed   lift 0.85 / 0.77   rhs 1.82 / 1.66
 //   a stage: 3D N = 2, 96x48x48, FP64 1.17 / 0.70; N = 5, 48x24x24, mixed 0.83 / 0.57;
 //   2D N = 4, 96x96, FP64 0.0376 / 0.0244
 // -------------------------------------------------------------------------
@@ -316,6 +331,22 @@ __device__ __forceinline__ void store_pair(T* elem, int p, T a, T b) {
     elem[2 * p] = a;
   else
     *reinterpret_cast<Pair<T>*>(elem + 2 * p) = Pair<T>{a, b};
+}
+
+// The same past the caches (nontemporal).
+typedef double DoublePair __attribute__((ext_vector_type(2), aligned(8)));
+template <int NN>
+__device__ __forceinline__ Pair<double> load_pair_nt(const double* elem, int p) {
+  const bool solo = pair_solo<NN>(p);
+  const DoublePair x = __builtin_nontemporal_load(reinterpret_cast<const DoublePair*>(elem + 2 * p - (solo ? 1 : 0)));
+  return Pair<double>{solo ? x.y : x.x, x.y};
+}
+template <int NN>
+__device__ __forceinline__ void store_pair_nt(double* elem, int p, double a, double b) {
+  if (pair_solo<NN>(p))
+    __builtin_nontemporal_store(a, elem + 2 * p);
+  else
+    __builtin_nontemporal_store(DoublePair{a, b}, reinterpret_cast<DoublePair*>(elem + 2 * p));
 }
 
 // The same in LDS (even positions; the second value of a lone last one
@@ -612,6 +643,19 @@ __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* _
 #pragma unroll
       for (int d = 0; d < DIM; ++d) div[h] += qd[h][d][d];
     }
+    // each component is stored as it is formed: collecting them first changes
+    // which products are fused, and so the FP32 roundings
+    const bool past = sizeof(GT) == sizeof(double) && (msh.stream & kStreamG);
+    auto store_g = [&](int k, GT a, GT b) {
+      GT* const g = G + (long long)k * S + o;
+      if constexpr (sizeof(GT) == sizeof(double)) {
+        if (past) {
+          store_pair_nt<NN>(g, nr.p, a, b);
+          return;
+        }
+      }
+      store_pair<NN>(g, nr.p, a, b);
+    };
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
@@ -622,11 +666,10 @@ __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* _
           t[h] = eps * (qd[h][b][a] + qd[h][a][b]);
           if (a == b) t[h] -= eps * R(2.0 / 3.0) * div[h];
         }
-        store_pair<NN>(G + (long long)tau_index<DIM>(a, b) * S + o, nr.p, GT(t[0]), GT(t[1]));
+        store_g(tau_index<DIM>(a, b), GT(t[0]), GT(t[1]));
       }
 #pragma unroll
-    for (int d = 0; d < DIM; ++d)
-      store_pair<NN>(G + (long long)(Sh::NTAU + d) * S + o, nr.p, GT(qd[0][d][DIM]), GT(qd[1][d][DIM]));
+    for (int d = 0; d < DIM; ++d) store_g(Sh::NTAU + d, GT(qd[0][d][DIM]), GT(qd[1][d][DIM]));
   }
 }
 
@@ -1149,8 +1192,13 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
 #pragma unroll
   for (int v = 0; v < NV; ++v) du_old[v] = Pair<double>{0.0, 0.0};
   if (e >= 0 && st.mode == 1 && st.A != 0.0) {
+    if (msh.stream & kStreamState) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) du_old[v] = load_pair<NN>(dU + v * S + o, nu.p);
+      for (int v = 0; v < NV; ++v) du_old[v] = load_pair_nt<NN>(dU + v * S + o, nu.p);
+    } else {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) du_old[v] = load_pair<NN>(dU + v * S + o, nu.p);
+    }
   }
   __syncthreads();
 
@@ -1194,14 +1242,28 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
         }
       }
     }
+    if (st.mode == 0) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) store_pair<NN>(Uout + v * S + o, nu.p, Rv[0][v], Rv[1][v]);
+      return;
+    }
+    double da[NV], db[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      if (st.mode == 0) {
-        store_pair<NN>(Uout + v * S + o, nu.p, Rv[0][v], Rv[1][v]);
-      } else {
-        const double da = st.A * du_old[v].a + st.dt * Rv[0][v], db = st.A * du_old[v].b + st.dt * Rv[1][v];
-        store_pair<NN>(dU + v * S + o, nu.p, da, db);
-        store_pair<NN>(Uout + v * S + o, nu.p, u[v].a + st.B * da, u[v].b + st.B * db);
+      da[v] = st.A * du_old[v].a + st.dt * Rv[0][v];
+      db[v] = st.A * du_old[v].b + st.dt * Rv[1][v];
+    }
+    if (msh.stream & kStreamState) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        store_pair_nt<NN>(dU + v * S + o, nu.p, da[v], db[v]);
+        store_pair_nt<NN>(Uout + v * S + o, nu.p, u[v].a + st.B * da[v], u[v].b + st.B * db[v]);
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        store_pair<NN>(dU + v * S + o, nu.p, da[v], db[v]);
+        store_pair<NN>(Uout + v * S + o, nu.p, u[v].a + st.B * da[v], u[v].b + st.B * db[v]);
       }
     }
   }

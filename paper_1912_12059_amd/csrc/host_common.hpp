@@ -279,6 +279,11 @@ BasisArgs basis_args(const nsk_ctx* c) {
   return b;
 }
 
+// bytes that the stages go through again and again: two states, dU and G
+double stage_bytes(const nsk_ctx* c) {
+  return double(c->S) * (24.0 * c->nvar + double(c->ng) * (c->par.precision == 0 ? 8.0 : 4.0));
+}
+
 MeshArgs mesh_args(const nsk_ctx* c) {
   MeshArgs m;
   for (int d = 0; d < 3; ++d) {
@@ -289,6 +294,7 @@ MeshArgs mesh_args(const nsk_ctx* c) {
   m.E = (int)c->E;
   m.S = c->S;
   m.nxcd = c->order == 0 ? 1 : kXcds;
+  m.stream = stream_bits(stage_bytes(c));
   return m;
 }
 
