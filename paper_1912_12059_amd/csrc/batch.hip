@@ -166,7 +166,8 @@ int upload_tables(nsk_batch* b) {
 // group's elements-per-workgroup variant)
 template <int NP, int EPB, typename R, typename GT>
 int launch_chunk_e(nsk_batch* b, const BatchGroup& g, int k, int parity, const StageArgs& st) {
-  using Tl = Tile<3, NP, EPB>;
+  constexpr int FORM = Staged<3, NP, R>::built ? kStaged : kLines;
+  using Tl = Tile<3, NP, EPB, FORM>;
   const BasisArgs bas = basis_args(b->ctx[g.inst[0]]);
   const PhysArgs ph = phys_args(b->ctx[g.inst[0]]);
   const BatchInst* desc = reinterpret_cast<const BatchInst*>(b->work + b->off_desc) + parity * b->ninst;
@@ -174,15 +175,15 @@ int launch_chunk_e(nsk_batch* b, const BatchGroup& g, int k, int parity, const S
   const int n = g.chunks[k + 1] - g.chunks[k];
   if (n <= 0) return NSK_OK;
   if (g.gridmul == 0) {
-    hipLaunchKernelGGL((lift_kernel_batch1<3, NP, EPB, R, GT>), dim3(n), dim3(Tl::THREADS), 0, b->stream, desc, items,
-                       bas, ph);
-    hipLaunchKernelGGL((rhs_kernel_batch1<3, NP, EPB, R, GT>), dim3(n), dim3(Tl::THREADS), 0, b->stream, desc, items,
-                       bas, ph, st);
+    hipLaunchKernelGGL((lift_kernel_batch1<3, NP, EPB, R, GT, FORM>), dim3(n), dim3(Tl::THREADS), 0, b->stream, desc,
+                       items, bas, ph);
+    hipLaunchKernelGGL((rhs_kernel_batch1<3, NP, EPB, R, GT, FORM>), dim3(n), dim3(Tl::THREADS), 0, b->stream, desc,
+                       items, bas, ph, st);
   } else {
     const int grid = std::min(n, b->ncu * g.gridmul);
-    hipLaunchKernelGGL((lift_kernel_batch<3, NP, EPB, R, GT>), dim3(grid), dim3(Tl::THREADS), 0, b->stream, desc,
+    hipLaunchKernelGGL((lift_kernel_batch<3, NP, EPB, R, GT, FORM>), dim3(grid), dim3(Tl::THREADS), 0, b->stream, desc,
                        items, n, bas, ph);
-    hipLaunchKernelGGL((rhs_kernel_batch<3, NP, EPB, R, GT>), dim3(grid), dim3(Tl::THREADS), 0, b->stream, desc,
+    hipLaunchKernelGGL((rhs_kernel_batch<3, NP, EPB, R, GT, FORM>), dim3(grid), dim3(Tl::THREADS), 0, b->stream, desc,
                        items, n, bas, ph, st);
   }
   return hipGetLastError() == hipSuccess ? NSK_OK : NSK_EHIP;
@@ -193,7 +194,8 @@ int launch_chunk_e(nsk_batch* b, const BatchGroup& g, int k, int parity, const S
 // arguments (no descriptor loads)
 template <int NP, int EPB, typename R, typename GT>
 int launch_single_e(nsk_batch* b, nsk_ctx* c, int parity, const StageArgs& st) {
-  using Tl = Tile<3, NP, EPB>;
+  constexpr int FORM = Staged<3, NP, R>::built ? kStaged : kLines;
+  using Tl = Tile<3, NP, EPB, FORM>;
   double* U2 = reinterpret_cast<double*>(c->work + c->off_U2);
   const double* Uin = parity ? U2 : c->U;
   double* Uout = parity ? c->U : U2;
@@ -203,10 +205,10 @@ int launch_single_e(nsk_batch* b, nsk_ctx* c, int parity, const StageArgs& st) {
   m.stream = batch_stream(b);
   const PhysArgs ph = phys_args(c);
   const unsigned blocks = (unsigned)((c->E + EPB - 1) / EPB);
-  hipLaunchKernelGGL((lift_kernel<3, NP, EPB, R, GT>), dim3(blocks), dim3(Tl::THREADS), 0, b->stream, Uin, G, bas, m,
-                     ph);
-  hipLaunchKernelGGL((rhs_kernel<3, NP, EPB, R, GT>), dim3(blocks), dim3(Tl::THREADS), 0, b->stream, Uin, G, Uout,
-                     c->dU, bas, m, ph, st);
+  hipLaunchKernelGGL((lift_kernel<3, NP, EPB, R, GT, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, b->stream, Uin, G, bas,
+                     m, ph);
+  hipLaunchKernelGGL((rhs_kernel<3, NP, EPB, R, GT, 0, 0, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, b->stream, Uin, G,
+                     Uout, c->dU, bas, m, ph, st);
   return hipGetLastError() == hipSuccess ? NSK_OK : NSK_EHIP;
 }
 

@@ -286,10 +286,16 @@ __device__ __forceinline__ constexpr int lds_step(int d) {
   return d == 2 && (NP == 2 || NP == 4) ? NP * NP + 2 : dstride<NP>(d);
 }
 
-template <int DIM, int NP, int EPB>
+// Forms of the line role: a lane a line, two lanes a line (LineEnd), or a lane a
+// line with the neighbours staged through LDS (NbPairs).
+constexpr int kLines = 0, kEnds = 1, kStaged = 2;
+
+template <int DIM, int NP, int EPB, int FORM = kLines>
 struct Tile {
   using Sh = Shape<DIM, NP>;
-  static constexpr int EPW = cmin(EPB, 64 / Sh::NF);       // elements of one wave in the line role
+  static constexpr int LPE = (FORM == kEnds ? 2 : 1) * Sh::NF;  // lanes of an element in the line role
+  static_assert(LPE <= 64, "a wave takes whole elements");
+  static constexpr int EPW = cmin(EPB, 64 / LPE);          // elements of one wave in the line role
   static constexpr int WPD = (EPB + EPW - 1) / EPW;        // waves per direction in the line role
   static constexpr int NPC = (Sh::NN + 1) / 2;             // node pairs per element
   static constexpr int THREADS = cmax(round64(EPB * NPC), 64 * DIM * WPD);
@@ -302,7 +308,7 @@ struct Tile {
 
 // In 1D a thread per node and one per face (dg_1d.hpp).
 template <int NP, int EPB>
-struct Tile<1, NP, EPB> {
+struct Tile<1, NP, EPB, kLines> {
   static constexpr int THREADS = round64(EPB * NP);
 };
 
@@ -407,18 +413,23 @@ __device__ __forceinline__ int elem_coord(const MeshArgs& m, int e) {
 // d-neighbours, face node f, the line's first node and 2/h.
 struct LineRole {
   int el = 0, e = -1, f = 0, base = 0;
+  int end = 0;  // with kEnds the end of the line that the lane takes: 0 xi = -1, 1 xi = +1
   int nb[2] = {0, 0};
   double h2 = 0.0;
 };
 
-template <int DIM, int NP, int EPB, int d>
+template <int DIM, int NP, int EPB, int d, int FORM = kLines>
 __device__ __forceinline__ LineRole line_role(const MeshArgs& m, int L, int sub, int lane,
                                               const int* __restrict__ skip) {
-  using Tl = Tile<DIM, NP, EPB>;
+  using Tl = Tile<DIM, NP, EPB, FORM>;
   constexpr int NF = Shape<DIM, NP>::NF;
   LineRole r;
-  const int k = lane / NF;
-  r.f = lane - k * NF;
+  const int k = lane / Tl::LPE;
+  r.f = lane - k * Tl::LPE;
+  if constexpr (FORM == kEnds) {
+    r.end = r.f >= NF ? 1 : 0;
+    r.f -= r.end * NF;
+  }
   r.el = sub * Tl::EPW + k;
   const int pos = L * EPB + r.el;
   if (k >= Tl::EPW || r.el >= EPB || pos >= m.E) return r;
@@ -437,14 +448,11 @@ __device__ __forceinline__ LineRole line_role(const MeshArgs& m, int L, int sub,
 // How a wave gets its neighbours' lines.  Mostly its lanes read them straight
 // from memory.  A line's values along x and y lie apart, which costs the L1 44
 // cycles an element and component instead of the 20 of whole elements read a
-// pair a lane; staging whole neighbours through LDS for that (into rows that
+// pair a lane; staging whole neighbours through LDS for that (kStaged, into rows that
 // the own values take afterwards) needs one more barrier and twice the LDS
-// traffic.  It wins where the lines are long and LDS values are four bytes: 3D
-// mixed precision, 0.77 against 0.79 ms a stage at N = 4 (64x32x32 elements) and
-// 0.57 against 0.62 at N = 5 (48x24x24); it loses at N = 3 (0.79 both), N = 2 (0.63
-// against 0.60) and in FP64 (N = 4 1.03 against 0.95, N = 2 0.83 against 0.70).
-template <int DIM, int NP, typename R>
-constexpr bool kStageNb = DIM == 3 && NP >= 5 && sizeof(R) == 4;
+// traffic.  It wins where the lines are long, LDS values are four bytes and the mesh
+// is large (Staged in host_common.hpp); it loses at N = 3 (0.79 ms both), N = 2
+// (0.63 against 0.60) and in FP64 (N = 4 1.03 against 0.95, N = 2 0.83 against 0.70).
 
 // Places of a wave's neighbour pairs, round by round: the pair p and its
 // position at in LDS (-1: none), and the two neighbours.
@@ -471,6 +479,54 @@ struct NbPairs {
   }
 };
 
+// Two lanes a line (kEnds).  One lane's chain, the loads of two neighbours' lines,
+// two fluxes and a contraction with every row, is the time of a launch that leaves
+// most of the chip idle (2D N = 6, 14x7 elements, FP64: lift 7.0 and rhs 10.5 us,
+// with two lanes 5.5 and 7.8; one direction after the other, a thread a node, took 5.1
+// and 8.1).  There each end of a line has a lane of its own, which
+// loads that end's neighbour (every load issued at once: registers are free),
+// forms that end's face values and, with the other end's by a shuffle, half of the
+// rows of the contraction: in the middle row of an odd number both lanes get the
+// same value.  The operations on a value and their order are those of one lane a
+// line, so the bits are the same.
+template <int NP>
+struct LineEnd {
+  static constexpr int H = (NP + 1) / 2;  // rows of a lane
+  bool hi;                                // the end xi = +1
+  int row0;                               // its first row
+  __device__ __forceinline__ explicit LineEnd(int end) : hi(end != 0), row0(end ? NP - H : 0) {}
+  // weights of the neighbour's and of the own trace at this end
+  template <typename T>
+  __device__ __forceinline__ T nb(const BasisOf<T>& B, int l) const { return hi ? B.Lm[l] : B.Lp[l]; }
+  template <typename T>
+  __device__ __forceinline__ T own(const BasisOf<T>& B, int l) const { return hi ? B.Lp[l] : B.Lm[l]; }
+  // a value of both ends from the lanes' own
+  template <int NF, typename T>
+  __device__ __forceinline__ void both(T x, int lane, T& lo, T& up) const {
+    const T y = __shfl(x, hi ? lane - NF : lane + NF, 64);
+    lo = hi ? y : x;
+    up = hi ? x : y;
+  }
+};
+
+// What row i of a contraction takes, for lanes of different rows: the derivative
+// matrix's row, then the K weights w_k[i] (in LDS: selecting between two scalar
+// copies of them cost 130 spilled scalar registers at N = 6).
+template <int NP, int K, bool ON, typename R>
+struct RowTable {
+  static constexpr int W = NP + K;
+  R v[ON ? NP : 1][ON ? W : 1];
+  __device__ __forceinline__ void fill(int tid, const BasisOf<R>& B, const R* const (&w)[K]) {
+    if constexpr (ON) {
+      if (tid < NP * NP) v[tid / NP][tid % NP] = B.Dhat[tid / NP][tid % NP];
+      if (tid < NP) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[tid][NP + k] = w[k][tid];
+      }
+    }
+  }
+};
+
 // x[v][l] = p[v * S + l * ST]: NVAL lines of a d-neighbour
 template <int NVAL, int NP, int ST, typename T>
 __device__ __forceinline__ void load_lines(const T* __restrict__ p, long long S, T (&x)[NVAL][NP]) {
@@ -486,22 +542,25 @@ __device__ __forceinline__ void load_lines(const T* __restrict__ p, long long S,
 //   q_d,i = (2/h_d) [ (L+_i w*_+ - L-_i w*_-) / omega_i - sum_l Dhat_il w_l ]
 // along each d-line, w* = (w_left + w_right) / 2 on the faces.
 // -------------------------------------------------------------------------
-template <int DIM, int NP, int EPB, typename R, typename GT, int MODEL>
+template <int DIM, int NP, int EPB, typename R, typename GT, int MODEL, int FORM>
 __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* __restrict__ U, GT* __restrict__ G,
                                                  const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph,
                                                  double* __restrict__ lfpart) {
   using Sh = Shape<DIM, NP>;
-  using Tl = Tile<DIM, NP, EPB>;
+  using Tl = Tile<DIM, NP, EPB, FORM>;
   constexpr int NN = Sh::NN, NL = Sh::NLIFT, SL = Tl::SL, PN = Tl::PN;
   constexpr int NV = MODEL == 1 ? DIM + 1 : DIM + 2;  // conserved variables
   constexpr int SI = MODEL == 1 ? 0 : DIM + 1;        // the lifted scalar: rho or c
   __shared__ __attribute__((aligned(16))) R sW[NL][SL];        // nodal primitives (v, s)
   __shared__ __attribute__((aligned(16))) R sX[DIM][NL][SL];   // per direction: gradients before the factor 2/h
+  constexpr bool ENDS = FORM == kEnds, STAGE = FORM == kStaged;
   __shared__ double sH2[EPB][DIM];
-  __shared__ int sNb[DIM][kStageNb<DIM, NP, R> ? EPB : 1][2];
+  __shared__ int sNb[DIM][STAGE ? EPB : 1][2];
+  __shared__ RowTable<NP, 3, ENDS, R> sT;
 
   const long long S = msh.S;
   const auto& B = bas.of(R());
+  sT.fill(tid, B, {B.Lp, B.Lm, B.invw});
   const NodeRole<DIM, NP, EPB> nr(tid);
   const int pos = L * EPB + nr.el;
   const bool active = nr.el < EPB && pos < msh.E;
@@ -516,14 +575,15 @@ __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* _
   const int dir = wv / Tl::WPD;
   const int sub = wv - dir * Tl::WPD, lane = tid & 63;
   // the neighbours' traces: the weights of xi = +1 before the element, of xi = -1 after it
-  R wn[2][NL];
+  R wn[2][NL];  // with kEnds wn[0]: that of the lane's end
+  double x1[ENDS ? NV : 1][NP];  // and its neighbour's line
   LineRole ln;
   static_for<DIM>([&](auto dc) {
     constexpr int d = decltype(dc)::value;
     if (dir != d) return;
-    ln = line_role<DIM, NP, EPB, d>(msh, L, sub, lane, nullptr);
+    ln = line_role<DIM, NP, EPB, d, FORM>(msh, L, sub, lane, nullptr);
     if (ln.e >= 0 && ln.f == 0) sH2[ln.el][d] = ln.h2;
-    if constexpr (kStageNb<DIM, NP, R>) {
+    if constexpr (STAGE) {
       const NbPairs<DIM, NP, EPB> np(ln, sub, lane, sNb[d]);
       const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
       static_for<2>([&](auto sc) {
@@ -558,6 +618,11 @@ __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* _
       return;
     }
     if (ln.e < 0) return;
+    if constexpr (ENDS) {
+      load_lines<NV, NP, dstride<NP>(d)>(U + (long long)(ln.end ? ln.nb[1] : ln.nb[0]) * NN + ln.base, S, x1);
+      __builtin_amdgcn_sched_barrier(0);
+      return;
+    }
     // every load of a line is issued before the first value is used
     static_for<2>([&](auto sc) {
       constexpr int s = decltype(sc)::value;
@@ -592,6 +657,21 @@ __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* _
       lfs = fmax(lf_node_speed<DIM>(ua, ph.T), lf_node_speed<DIM>(ub, ph.T));
     }
   }
+  if constexpr (ENDS) {
+    if (ln.e >= 0) {
+      const LineEnd<NP> end(ln.end);
+#pragma unroll
+      for (int k = 0; k < NL; ++k) wn[0][k] = R(0);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const double irho = 1.0 / x1[0][l];
+        const R lw = end.nb(B, l);
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) wn[0][k] += lw * R(x1[1 + k][l] * irho);
+        wn[0][DIM] += lw * R(x1[SI][l]);
+      }
+    }
+  }
   if constexpr (MODEL == 1) {
     __shared__ double sRed[(Tl::THREADS + 63) / 64];
     if (lfpart) block_max_store<Tl::THREADS>(lfs, sRed, lfpart + L, tid);
@@ -602,6 +682,29 @@ __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* _
     constexpr int d = decltype(dc)::value;
     if (dir != d || ln.e < 0) return;
     const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+    if constexpr (ENDS) {
+      const LineEnd<NP> end(ln.end);
+#pragma unroll
+      for (int k = 0; k < NL; ++k) {
+        R w[NP], wo = R(0), wsm, wsp;
+#pragma unroll
+        for (int l = 0; l < NP; ++l) {
+          w[l] = sW[k][b0 + l * lds_step<NP>(d)];
+          wo += end.own(B, l) * w[l];
+        }
+        end.template both<Sh::NF>(R(0.5) * (wo + wn[0][k]), lane, wsm, wsp);
+#pragma unroll
+        for (int r = 0; r < end.H; ++r) {
+          R vol = R(0);
+#pragma unroll
+          for (int l = 0; l < NP; ++l) vol += sT.v[end.row0 + r][l] * w[l];
+          const R* const x = &sT.v[end.row0 + r][NP];
+          const R surf = (x[0] * wsp - x[1] * wsm) * x[2];
+          sX[d][k][b0 + (end.row0 + r) * lds_step<NP>(d)] = surf - vol;
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
       R w[NP], wl = R(0), wr = R(0);
@@ -683,17 +786,20 @@ __device__ __forceinline__ void lift_block_lines(int L, int tid, const double* _
 // Korteweg stress of Sec. 2.2 in conservative form).  The gradient slots are
 // only read, so neighbouring workgroups see the first lifting's values.
 // -------------------------------------------------------------------------
-template <int DIM, int NP, int EPB>
+template <int DIM, int NP, int EPB, int FORM>
 __device__ __forceinline__ void lap_block_lines(int L, int tid, const double* __restrict__ U, double* __restrict__ G,
                                           const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph) {
   using Sh = Shape<DIM, NP>;
-  using Tl = Tile<DIM, NP, EPB>;
+  using Tl = Tile<DIM, NP, EPB, FORM>;
   constexpr int NN = Sh::NN, NT = Sh::NTAU, SL = Tl::SL, PN = Tl::PN;
   __shared__ __attribute__((aligned(16))) double sg[DIM][SL];   // own g_d; a d-line's lane overwrites it with the contribution to lap
   __shared__ double sH2[EPB][DIM];
+  constexpr bool ENDS = FORM == kEnds;
+  __shared__ RowTable<NP, 3, ENDS, double> sT;
 
   const long long S = msh.S;
   const auto& B = bas.of(double());
+  sT.fill(tid, B, {B.Lp, B.Lm, B.invw});
   const NodeRole<DIM, NP, EPB> nr(tid);
   const int pos = L * EPB + nr.el;
   const bool active = nr.el < EPB && pos < msh.E;
@@ -710,14 +816,20 @@ __device__ __forceinline__ void lap_block_lines(int L, int tid, const double* __
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int dir = wv / Tl::WPD;
   const int sub = wv - dir * Tl::WPD, lane = tid & 63;
-  double gn[2] = {0.0, 0.0};
+  double gn[2] = {0.0, 0.0};  // with kEnds gn[0]: that of the lane's end
+  double x1[1][NP];           // and its neighbour's line
   LineRole ln;
   static_for<DIM>([&](auto dc) {
     constexpr int d = decltype(dc)::value;
     if (dir != d) return;
-    ln = line_role<DIM, NP, EPB, d>(msh, L, sub, lane, nullptr);
+    ln = line_role<DIM, NP, EPB, d, FORM>(msh, L, sub, lane, nullptr);
     if (ln.e < 0) return;
     if (ln.f == 0) sH2[ln.el][d] = ln.h2;
+    if constexpr (ENDS) {
+      load_lines<1, NP, dstride<NP>(d)>(
+          G + (long long)(NT + d) * S + (long long)(ln.end ? ln.nb[1] : ln.nb[0]) * NN + ln.base, S, x1);
+      return;
+    }
     double x[2][1][NP];
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -734,12 +846,40 @@ __device__ __forceinline__ void lap_block_lines(int L, int tid, const double* __
       lds_put(&sg[d][nr.sl], g[d].a, g[d].b);
     }
   }
+  if constexpr (ENDS) {
+    if (ln.e >= 0) {
+      const LineEnd<NP> end(ln.end);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) gn[0] += end.nb(B, l) * x1[0][l];
+    }
+  }
   __syncthreads();
 
   static_for<DIM>([&](auto dc) {
     constexpr int d = decltype(dc)::value;
     if (dir != d || ln.e < 0) return;
     const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+    if constexpr (ENDS) {
+      const LineEnd<NP> end(ln.end);
+      double w[NP], wo = 0.0, gm, gp;
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        w[l] = sg[d][b0 + l * lds_step<NP>(d)];
+        wo += end.own(B, l) * w[l];
+      }
+      end.template both<Sh::NF>(0.5 * (wo + gn[0]), lane, gm, gp);
+      wave_fence();  // both lanes have read the line that they overwrite
+#pragma unroll
+      for (int r = 0; r < end.H; ++r) {
+        double vol = 0.0;
+#pragma unroll
+        for (int l = 0; l < NP; ++l) vol += sT.v[end.row0 + r][l] * w[l];
+        const double* const x = &sT.v[end.row0 + r][NP];
+        const double surf = (x[0] * gp - x[1] * gm) * x[2];
+        sg[d][b0 + (end.row0 + r) * lds_step<NP>(d)] = surf - vol;
+      }
+      return;
+    }
     double w[NP], wl = 0.0, wr = 0.0;
 #pragma unroll
     for (int l = 0; l < NP; ++l) {
@@ -870,12 +1010,12 @@ __device__ __forceinline__ void face_flux(const R* uL, const R* uR, const R* vLR
 
 constexpr int kLineGroup = 3;
 
-template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX, int MODEL>
+template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX, int MODEL, int FORM>
 __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __restrict__ U, const GT* __restrict__ G,
                                           double* __restrict__ Uout, double* __restrict__ dU, const BasisArgs& bas,
                                           const MeshArgs& msh, const PhysArgs& ph, const StageArgs& st) {
   using Sh = Shape<DIM, NP>;
-  using Tl = Tile<DIM, NP, EPB>;
+  using Tl = Tile<DIM, NP, EPB, FORM>;
   constexpr int NN = Sh::NN, NT = Sh::NTAU, SL = Tl::SL, PN = Tl::PN;
   constexpr int NV = MODEL == 1 ? DIM + 1 : DIM + 2;   // conserved variables
   constexpr int NG = MODEL == 1 ? NT : Sh::NG;         // G slots read: Sigma, or (tau, grad c)
@@ -886,7 +1026,7 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   // same memory takes the directions' contributions
   constexpr int IP = NV + NG, II = IP + 1;
   constexpr int ROWS = cmax(NV + NG + 2, DIM * NV);
-  constexpr bool STAGE = kStageNb<DIM, NP, R>;
+  constexpr bool ENDS = FORM == kEnds, STAGE = FORM == kStaged;
   // A pair's own values stay in registers to the end: 8 of the 81 components that
   // an element asks the L1 for, whose outstanding misses bound this kernel in 3D
   // (147 M lines of 128 bytes at 74 in flight a CU on average and 574 cycles, 96x48x48
@@ -894,6 +1034,11 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   // matter more: with staged neighbours (1.80 against 1.74 ms there in mixed
   // precision), and with HLLC at N = 1 (384 against 373 us a stage, 120x60x60).
   constexpr bool AGAIN = STAGE || (NP == 2 && FLUX == 1);
+  // With two lanes a line in 2D every load of the kernel is issued before the first
+  // is waited for, unless that takes more registers than three waves a SIMD have
+  // (N = 6 in FP64: 182; 3D: 204) or a fourth wave (MODEL 1: N = 4, 141x71, a stage
+  // 33.2 -> 36.0 us).
+  constexpr bool EARLY = ENDS && DIM == 2 && MODEL == 0 && (NP < 7 || MIXED);
   constexpr int RPD = ROWS / DIM;  // rows in which a direction's waves stage neighbours
   static_assert(!STAGE || (RPD >= NV && RPD >= NVX), "staging rows");
   __shared__ __attribute__((aligned(16))) R sIn[ROWS][SL];
@@ -901,9 +1046,11 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   __shared__ int sNb[DIM][STAGE ? EPB : 1][2];
   __shared__ double sH2[EPB][DIM];
   __shared__ int sE[AGAIN ? EPB : 1];  // element of each slot, -1: none
+  __shared__ RowTable<NP, 2, ENDS, R> sT;
 
   const long long S = msh.S;
   const auto& B = bas.of(R());
+  sT.fill(tid, B, {B.wm, B.wp});
   const NodeRole<DIM, NP, EPB> nr(tid);
   const int pos = L * EPB + nr.el;
   int e = nr.el < EPB && pos < msh.E ? msh.order[pos] : -1;
@@ -937,17 +1084,19 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   };
   if constexpr (!STAGE) {
     load_own();
-    put_own();
+    if constexpr (!EARLY) put_own();
   }
 
-  // line role: the neighbours' traces
+  // line role: the neighbours' traces (with kEnds [0]: that of the lane's end)
   R un[2][NV], vn[2][NVX];
   double rn[2] = {0.0, 0.0};  // density traces in FP64 (EoS guard)
   LineRole ln;
+  double xu1[ENDS ? NV : 1][NP];  // with kEnds the neighbour's line
+  GT xg1[ENDS ? NVX : 1][NP];
   static_for<DIM>([&](auto dc) {
     constexpr int d = decltype(dc)::value;
     if (dir != d) return;
-    ln = line_role<DIM, NP, EPB, d>(msh, L, sub, lane, st.skip);
+    ln = line_role<DIM, NP, EPB, d, FORM>(msh, L, sub, lane, st.skip);
     if (ln.e >= 0 && ln.f == 0) sH2[ln.el][d] = ln.h2;
     if constexpr (STAGE) {
       // U, then the viscous components, of each side, in the rows of the
@@ -1032,6 +1181,16 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
       return;
     }
     if (ln.e < 0) return;
+    if constexpr (ENDS) {
+      const long long on = (long long)(ln.end ? ln.nb[1] : ln.nb[0]) * NN + ln.base;
+      load_lines<NV, NP, dstride<NP>(d)>(U + on, S, xu1);
+#pragma unroll
+      for (int k = 0; k < NVX; ++k)
+#pragma unroll
+        for (int l = 0; l < NP; ++l)
+          xg1[k][l] = (G + (long long)(k < DIM ? tau_index<DIM>(k, d) : NT + d) * S + on)[l * dstride<NP>(d)];
+      return;
+    }
     // components in groups of kLineGroup, the loads of a group issued two
     // groups before their use
     constexpr int NC = NV + NVX, NGRP = (2 * NC + kLineGroup - 1) / kLineGroup;
@@ -1075,6 +1234,44 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
       __builtin_amdgcn_sched_barrier(0);
     });
   });
+  Pair<double> du_old[NV];
+  auto load_du = [&](long long o, int p) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) du_old[v] = Pair<double>{0.0, 0.0};
+    if (e >= 0 && st.mode == 1 && st.A != 0.0) {
+      if (msh.stream & kStreamState) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) du_old[v] = load_pair_nt<NN>(dU + v * S + o, p);
+      } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) du_old[v] = load_pair<NN>(dU + v * S + o, p);
+      }
+    }
+  };
+  if constexpr (EARLY) {
+    load_du((long long)cmax(e, 0) * NN, nr.p);
+    __builtin_amdgcn_sched_barrier(0);
+    put_own();
+  }
+  if constexpr (ENDS) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (ln.e >= 0) {
+      const LineEnd<NP> end(ln.end);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) un[0][v] = R(0);
+#pragma unroll
+      for (int k = 0; k < NVX; ++k) vn[0][k] = R(0);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const R lw = end.nb(B, l);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) un[0][v] += lw * R(xu1[v][l]);
+        if (MIXED) rn[0] += end.nb(bas.d, l) * xu1[0][l];
+#pragma unroll
+        for (int k = 0; k < NVX; ++k) vn[0][k] += lw * R(xg1[k][l]);
+      }
+    }
+  }
   if constexpr (STAGE) {
     load_own();
     __syncthreads();  // the neighbours are folded: their rows take the own values
@@ -1083,11 +1280,71 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   __syncthreads();
 
   // line role: numerical fluxes at both ends, contraction of the nodal flux
-  R t[NP][NV];
+  R t[ENDS ? (NP + 1) / 2 : NP][NV];
   static_for<DIM>([&](auto dc) {
     constexpr int d = decltype(dc)::value;
     if (dir != d || ln.e < 0) return;
     const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+    if constexpr (ENDS) {
+      const LineEnd<NP> end(ln.end);
+      R uo[NV], uL[NV], uR[NV], Fe[NV], F0[NV], F1[NV];
+      double ro = 0.0;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        uo[v] = R(0);
+#pragma unroll
+        for (int l = 0; l < NP; ++l) uo[v] += end.own(B, l) * sIn[v][b0 + l * lds_step<NP>(d)];
+        uL[v] = end.hi ? uo[v] : un[0][v];
+        uR[v] = end.hi ? un[0][v] : uo[v];
+      }
+#pragma unroll
+      for (int k = 0; k < NVX; ++k) {
+        R vo = R(0);
+#pragma unroll
+        for (int l = 0; l < NP; ++l)
+          vo += end.own(B, l) * sIn[NV + (k < DIM ? tau_index<DIM>(k, d) : NT + d)][b0 + l * lds_step<NP>(d)];
+        vn[0][k] += vo;
+      }
+      if constexpr (MIXED) {
+#pragma unroll
+        for (int l = 0; l < NP; ++l) ro += end.own(bas.d, l) * sRho64[0][b0 + l * lds_step<NP>(d)];
+      } else {
+        ro = uo[0];
+        rn[0] = un[0][0];
+      }
+      face_flux<DIM, R, FLUX, MODEL, d, NV, NVX>(uL, uR, vn[0], end.hi ? ro : rn[0], end.hi ? rn[0] : ro, lam_g, kb, ph,
+                                                 Fe);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) end.template both<Sh::NF>(Fe[v], lane, F0[v], F1[v]);
+#pragma unroll
+      for (int r = 0; r < end.H; ++r)
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+          t[r][v] = MIXED ? R(0) : sT.v[end.row0 + r][NP] * F0[v] - sT.v[end.row0 + r][NP + 1] * F1[v];
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const int b = b0 + l * lds_step<NP>(d);
+        R u[NV], F[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[v] = sIn[v][b];
+        conv_flux<DIM, R, NV>(d, u, sIn[II][b], sIn[IP][b], F);
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) F[1 + j] -= sIn[NV + tau_index<DIM>(j, d)][b];
+        if constexpr (MODEL == 0) F[DIM + 1] -= kb * sIn[NV + NT + d][b];
+#pragma unroll
+        for (int r = 0; r < end.H; ++r)
+#pragma unroll
+          for (int v = 0; v < NV; ++v) t[r][v] += sT.v[end.row0 + r][l] * F[v];
+      }
+      if constexpr (MIXED) {
+#pragma unroll
+        for (int r = 0; r < end.H; ++r)
+#pragma unroll
+          for (int v = 0; v < NV; ++v)
+            t[r][v] = t[r][v] - (sT.v[end.row0 + r][NP + 1] * F1[v] - sT.v[end.row0 + r][NP] * F0[v]);
+      }
+      return;
+    }
     // own traces at both ends (0: xi = -1, 1: xi = +1), one pass over the line
     R uo[2][NV], Fs[2][NV];
     double ro[2] = {0.0, 0.0};
@@ -1167,16 +1424,17 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
     constexpr int d = decltype(dc)::value;
     if (dir != d || ln.e < 0) return;
     const int b0 = ln.el * PN + lds_slot<NP>(ln.base);
+    constexpr int ROWS_OF_LANE = ENDS ? (NP + 1) / 2 : NP;
+    const int row0 = ENDS ? LineEnd<NP>(ln.end).row0 : 0;
 #pragma unroll
-    for (int i = 0; i < NP; ++i)
+    for (int i = 0; i < ROWS_OF_LANE; ++i)
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sIn[d * NV + v][b0 + i * lds_step<NP>(d)] = t[i][v];
+      for (int v = 0; v < NV; ++v) sIn[d * NV + v][b0 + (row0 + i) * lds_step<NP>(d)] = t[i][v];
   });
 
   const NodeRole<DIM, NP, EPB> nu(AGAIN ? opaque(tid) : tid);
   if constexpr (AGAIN) e = nu.el < EPB ? sE[nu.el] : -1;
   const long long o = (long long)cmax(e, 0) * NN;
-  Pair<double> du_old[NV];
   Pair<double> ua[AGAIN ? NV : 1];
   Pair<GT> ga[AGAIN ? DIM : 1];
   Pair<double>* const u = AGAIN ? ua : u0;
@@ -1189,17 +1447,7 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
       for (int d = 0; MODEL == 0 && d < DIM; ++d) ga[d] = load_pair<NN>(G + (long long)(NT + d) * S + o, nu.p);
     }
   }
-#pragma unroll
-  for (int v = 0; v < NV; ++v) du_old[v] = Pair<double>{0.0, 0.0};
-  if (e >= 0 && st.mode == 1 && st.A != 0.0) {
-    if (msh.stream & kStreamState) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) du_old[v] = load_pair_nt<NN>(dU + v * S + o, nu.p);
-    } else {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) du_old[v] = load_pair<NN>(dU + v * S + o, nu.p);
-    }
-  }
+  if constexpr (!EARLY) load_du(o, nu.p);
   __syncthreads();
 
   // source (FP64) and update
@@ -1275,42 +1523,43 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
 
 namespace nsk {
 
-template <int DIM, int NP, int EPB, typename R, typename GT, int MODEL = 0>
+template <int DIM, int NP, int EPB, typename R, typename GT, int MODEL = 0, int FORM = kLines>
 __device__ __forceinline__ void lift_block(int L, int tid, const double* __restrict__ U, GT* __restrict__ G,
                                            const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph,
                                            double* __restrict__ lfpart = nullptr) {
   if constexpr (DIM == 1)
     lift_block_1d<NP, EPB, R, GT, MODEL>(L, tid, U, G, bas, msh, ph, lfpart);
   else
-    lift_block_lines<DIM, NP, EPB, R, GT, MODEL>(L, tid, U, G, bas, msh, ph, lfpart);
+    lift_block_lines<DIM, NP, EPB, R, GT, MODEL, FORM>(L, tid, U, G, bas, msh, ph, lfpart);
 }
 
-template <int DIM, int NP, int EPB>
+template <int DIM, int NP, int EPB, int FORM>
 __device__ __forceinline__ void lap_block(int L, int tid, const double* __restrict__ U, double* __restrict__ G,
                                           const BasisArgs& bas, const MeshArgs& msh, const PhysArgs& ph) {
   if constexpr (DIM == 1)
     lap_block_1d<NP, EPB>(L, tid, U, G, bas, msh, ph);
   else
-    lap_block_lines<DIM, NP, EPB>(L, tid, U, G, bas, msh, ph);
+    lap_block_lines<DIM, NP, EPB, FORM>(L, tid, U, G, bas, msh, ph);
 }
 
-template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX = 0, int MODEL = 0>
+template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX = 0, int MODEL = 0, int FORM = kLines>
 __device__ __forceinline__ void rhs_block(int L, int tid, const double* __restrict__ U, const GT* __restrict__ G,
                                           double* __restrict__ Uout, double* __restrict__ dU, const BasisArgs& bas,
                                           const MeshArgs& msh, const PhysArgs& ph, const StageArgs& st) {
   if constexpr (DIM == 1)
     rhs_block_1d<NP, EPB, R, GT, FLUX, MODEL>(L, tid, U, G, Uout, dU, bas, msh, ph, st);
   else
-    rhs_block_lines<DIM, NP, EPB, R, GT, FLUX, MODEL>(L, tid, U, G, Uout, dU, bas, msh, ph, st);
+    rhs_block_lines<DIM, NP, EPB, R, GT, FLUX, MODEL, FORM>(L, tid, U, G, Uout, dU, bas, msh, ph, st);
 }
 
 // -------------------------------------------------------------------------
 // One launch per stage kernel over a single mesh.
 // -------------------------------------------------------------------------
-template <int DIM, int NP, int EPB, typename R, typename GT>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS))
+template <int DIM, int NP, int EPB, typename R, typename GT, int FORM = kLines>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
 lift_kernel(const double* __restrict__ U, GT* __restrict__ G, BasisArgs bas, MeshArgs msh, PhysArgs ph) {
-  lift_block<DIM, NP, EPB, R, GT>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, bas, msh, ph);
+  lift_block<DIM, NP, EPB, R, GT, 0, FORM>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, bas, msh,
+                                           ph);
 }
 
 // The right-hand-side kernels are held to 3 waves per SIMD (168 VGPRs), where
@@ -1320,30 +1569,31 @@ lift_kernel(const double* __restrict__ U, GT* __restrict__ G, BasisArgs bas, Mes
 // 96x48x48 elements); 2 waves lose (2.41 against 2.14 ms; degree 5, 48x24x24, a
 // stage: 0.86 against 0.73 ms).
 constexpr int kRhsWaves = 3;
-template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX = 0, int MODEL = 0>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves)))
+template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX = 0, int MODEL = 0, int FORM = kLines>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
+    __attribute__((amdgpu_waves_per_eu(kRhsWaves)))
 rhs_kernel(const double* __restrict__ U, const GT* __restrict__ G, double* __restrict__ Uout,
            double* __restrict__ dU, BasisArgs bas, MeshArgs msh, PhysArgs ph, StageArgs st) {
-  rhs_block<DIM, NP, EPB, R, GT, FLUX, MODEL>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, Uout,
-                                              dU, bas, msh, ph, st);
+  rhs_block<DIM, NP, EPB, R, GT, FLUX, MODEL, FORM>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G,
+                                                     Uout, dU, bas, msh, ph, st);
 }
 
 // Original NSK path: the first lifting, which also writes the workgroup's
 // maximum of the global Lax-Friedrichs speed to lfpart[logical block] (when
 // lfpart is set) ...
-template <int DIM, int NP, int EPB>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS))
+template <int DIM, int NP, int EPB, int FORM = kLines>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
 nsk_lift_kernel(const double* __restrict__ U, double* __restrict__ G, BasisArgs bas, MeshArgs msh, PhysArgs ph,
                 double* __restrict__ lfpart) {
-  lift_block<DIM, NP, EPB, double, double, 1>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, bas,
-                                              msh, ph, lfpart);
+  lift_block<DIM, NP, EPB, double, double, 1, FORM>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G,
+                                                     bas, msh, ph, lfpart);
 }
 
 // ... the second lifting ...
-template <int DIM, int NP, int EPB>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS))
+template <int DIM, int NP, int EPB, int FORM = kLines>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
 lap_kernel(const double* __restrict__ U, double* __restrict__ G, BasisArgs bas, MeshArgs msh, PhysArgs ph) {
-  lap_block<DIM, NP, EPB>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, bas, msh, ph);
+  lap_block<DIM, NP, EPB, FORM>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G, bas, msh, ph);
 }
 
 // ... and the maximum of the partial speeds, in two launches: kMaxReduceBlocks
@@ -1388,23 +1638,23 @@ struct BatchItem {
 // in rounds of gridDim.x consecutive items.  In both, each XCD takes a
 // contiguous slice of the items in flight, so neighbouring elements meet in
 // the same L2.
-template <int DIM, int NP, int EPB, typename R, typename GT>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS))
+template <int DIM, int NP, int EPB, typename R, typename GT, int FORM>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
 lift_kernel_batch1(const BatchInst* __restrict__ inst, const BatchItem* __restrict__ items, BasisArgs bas,
                    PhysArgs ph) {
   const BatchItem w = items[remap_block(blockIdx.x, gridDim.x, kBatchXcds)];
   const BatchInst& I = inst[w.inst];
-  lift_block<DIM, NP, EPB, R, GT>(w.L, threadIdx.x, I.U, reinterpret_cast<GT*>(I.G), bas, I.msh, ph);
+  lift_block<DIM, NP, EPB, R, GT, 0, FORM>(w.L, threadIdx.x, I.U, reinterpret_cast<GT*>(I.G), bas, I.msh, ph);
 }
 
-template <int DIM, int NP, int EPB, typename R, typename GT>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves)))
+template <int DIM, int NP, int EPB, typename R, typename GT, int FORM>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves)))
 rhs_kernel_batch1(const BatchInst* __restrict__ inst, const BatchItem* __restrict__ items, BasisArgs bas,
                   PhysArgs ph, StageArgs st) {
   const BatchItem w = items[remap_block(blockIdx.x, gridDim.x, kBatchXcds)];
   const BatchInst& I = inst[w.inst];
-  rhs_block<DIM, NP, EPB, R, GT>(w.L, threadIdx.x, I.U, reinterpret_cast<const GT*>(I.G), I.Uout, I.dU, bas, I.msh,
-                                 ph, st);
+  rhs_block<DIM, NP, EPB, R, GT, 0, 0, FORM>(w.L, threadIdx.x, I.U, reinterpret_cast<const GT*>(I.G), I.Uout, I.dU, bas,
+                                             I.msh, ph, st);
 }
 
 // The thread index handed to the block functions is made opaque in every
@@ -1417,8 +1667,8 @@ __device__ __forceinline__ int opaque_tid() {
   return t;
 }
 
-template <int DIM, int NP, int EPB, typename R, typename GT>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS))
+template <int DIM, int NP, int EPB, typename R, typename GT, int FORM>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
 lift_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restrict__ items, int nitems,
                   BasisArgs bas, PhysArgs ph) {
   const int slot = remap_block(blockIdx.x, gridDim.x, kBatchXcds);
@@ -1427,14 +1677,14 @@ lift_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restric
     if (it < nitems) {
       const BatchItem w = items[it];
       const BatchInst& I = inst[w.inst];
-      lift_block<DIM, NP, EPB, R, GT>(w.L, opaque_tid(), I.U, reinterpret_cast<GT*>(I.G), bas, I.msh, ph);
+      lift_block<DIM, NP, EPB, R, GT, 0, FORM>(w.L, opaque_tid(), I.U, reinterpret_cast<GT*>(I.G), bas, I.msh, ph);
     }
     __syncthreads();  // LDS is reused by the next item
   }
 }
 
-template <int DIM, int NP, int EPB, typename R, typename GT>
-__global__ void __launch_bounds__((Tile<DIM, NP, EPB>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves)))
+template <int DIM, int NP, int EPB, typename R, typename GT, int FORM>
+__global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS)) __attribute__((amdgpu_waves_per_eu(kRhsWaves)))
 rhs_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restrict__ items, int nitems,
                  BasisArgs bas, PhysArgs ph, StageArgs st) {
   const int slot = remap_block(blockIdx.x, gridDim.x, kBatchXcds);
@@ -1443,8 +1693,8 @@ rhs_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restrict
     if (it < nitems) {
       const BatchItem w = items[it];
       const BatchInst& I = inst[w.inst];
-      rhs_block<DIM, NP, EPB, R, GT>(w.L, opaque_tid(), I.U, reinterpret_cast<const GT*>(I.G), I.Uout, I.dU, bas,
-                                     I.msh, ph, st);
+      rhs_block<DIM, NP, EPB, R, GT, 0, 0, FORM>(w.L, opaque_tid(), I.U, reinterpret_cast<const GT*>(I.G), I.Uout,
+                                                 I.dU, bas, I.msh, ph, st);
     }
     __syncthreads();
   }

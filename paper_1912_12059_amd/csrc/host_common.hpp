@@ -382,4 +382,48 @@ void subcell_matrices(const Basis1D& b, double M[kMaxNP][kMaxNP], double Minv[kM
       V[k][i] = b.w[i] * std::sqrt(k + 0.5) * (double)P;
     }
 }
+
+// Launches whose lines take two lanes each (kEnds in dg_kernels.hpp): from degree 4
+// in 2D, and degree 4 in 3D (at degree 5 an element has more than 64 line ends; up to
+// degree 3 one lane's chain is short enough), while the chip is not full of them.  A
+// workgroup is one wave of line ends a direction.  The limits, in workgroups of this
+// form, lie where both forms are equal.  Measured, us for four steps, one lane a line
+// / two:
+//   2D N = 4  20x10 FP64 263 / 219, mixed 247 / 216; 54x27 259 / 225; 69x35 320 / 275;
+//             98x49 369 / 346, mixed 345 / 325; 110x55 390 / 355; 141x71 527 / 538
+//   2D N = 5  17x8 277 / 211, mixed 251 / 217; 183x91 1014 / 891, mixed 831 / 819;
+//             258x129 783 / 725, mixed 657 / 688
+//   2D N = 6  14x7 341 / 242, mixed 277 / 238; 156x78 1212 / 960, 938 / 849; 350x175
+//             2186 / 2235
+//   3D N = 4  7x3x3 334 / 255, mixed 354 / 247; 16x8x8 524 / 488, 471 / 426; 19x9x9
+//             676 / 705, mixed 558 / 624
+// In 2D at degree 4, and in mixed precision, the other form's fewer workgroups are
+// faster where they are one a CU and this form's are more: 59x29 N = 4 259 / 272,
+// mixed 242 / 258; 49x25 N = 6 mixed 286 / 290.
+template <int DIM, int NP>
+struct Ends {
+  using Sh = Shape<DIM, NP>;
+  static constexpr bool built = DIM > 1 && NP > 4 && 2 * Sh::NF <= 64;
+  static constexpr int EPB = built ? 64 / (2 * Sh::NF) : 1;
+  static constexpr int most = NP == 5 ? 1024 : NP == 6 ? 4096 : 6144;
+  static bool pays(const nsk_ctx* c) {
+    constexpr int cus = 256;
+    const long long mine = (c->E + EPB - 1) / EPB, other = (c->E + Epb<DIM, NP>::V0 - 1) / Epb<DIM, NP>::V0;
+    if (DIM == 2 && (NP == 5 || c->par.precision == 1) && mine > cus && other <= cus) return false;
+    return mine <= most;
+  }
+};
+
+// Neighbours staged through LDS (kStaged): 3D in mixed precision from degree 4, from
+// the number of elements on where both forms are equal.  Measured, us for four steps
+// (from a million nodes two), a lane a line / staged: N = 4 32x16x16 855 / 906,
+// 40x20x20 1674 / 1671, 58x29x29 5595 / 5509; N = 5 12x6x6 455 / 478, 13x7x7 553 / 542,
+// 18x9x9 863 / 827, 33x17x17 1967 / 1836.
+template <int DIM, int NP, typename R>
+struct Staged {
+  static constexpr bool built = DIM == 3 && NP >= 5 && sizeof(R) == 4;
+  static constexpr int least = NP == 5 ? 16000 : 500;
+  static bool pays(const nsk_ctx* c) { return c->E >= least; }
+};
+
 }  // namespace

@@ -49,9 +49,9 @@ ClosureArgs closure_args_of(const nsk_ctx* c) {
 // Original NSK path: first lifting (with the per-workgroup maxima of the
 // global Lax-Friedrichs speed), their reduction, the second lifting, then the
 // right-hand side with the global Lax-Friedrichs flux.
-template <int DIM, int NP, int EPB>
+template <int DIM, int NP, int EPB, int FORM>
 int launch_stage_nsk(nsk_ctx* c, const double* Uin, double* Uout, double* dU, const StageArgs& st) {
-  using Tl = Tile<DIM, NP, EPB>;
+  using Tl = Tile<DIM, NP, EPB, FORM>;
   const BasisArgs b = basis_args(c);
   const MeshArgs m = mesh_args(c);
   const PhysArgs p = phys_args(c);
@@ -64,19 +64,19 @@ int launch_stage_nsk(nsk_ctx* c, const double* Uin, double* Uout, double* dU, co
   const unsigned blocks = (unsigned)((c->E + EPB - 1) / EPB);
   hipEvent_t* ev = stage_events(c, st);
   if (ev) (void)hipEventRecord(ev[0], c->stream);
-  hipLaunchKernelGGL((nsk_lift_kernel<DIM, NP, EPB>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b, m, p,
-                     lfpart);
+  hipLaunchKernelGGL((nsk_lift_kernel<DIM, NP, EPB, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b, m,
+                     p, lfpart);
   if (ev) (void)hipEventRecord(ev[1], c->stream);
   hipLaunchKernelGGL(max_reduce_kernel<kMaxReduceThreads>, dim3(kMaxReduceBlocks), dim3(kMaxReduceThreads), 0,
                      c->stream, lfpart, (int)blocks, lf2);
   hipLaunchKernelGGL(max_reduce_kernel<kMaxReduceThreads>, dim3(1), dim3(kMaxReduceThreads), 0, c->stream, lf2,
                      kMaxReduceBlocks, lf);
-  hipLaunchKernelGGL((lap_kernel<DIM, NP, EPB>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b, m, p);
+  hipLaunchKernelGGL((lap_kernel<DIM, NP, EPB, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b, m, p);
   if (ev) (void)hipEventRecord(ev[2], c->stream);
   StageArgs sta = st;
   sta.lf = lf;
-  hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, double, double, 2, 1>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream,
-                     Uin, G, Uout, dU, b, m, p, sta);
+  hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, double, double, 2, 1, FORM>), dim3(blocks), dim3(Tl::THREADS), 0,
+                     c->stream, Uin, G, Uout, dU, b, m, p, sta);
   if (ev) (void)hipEventRecord(ev[3], c->stream);
   return hipGetLastError() == hipSuccess ? NSK_OK : NSK_EHIP;
 }
@@ -98,9 +98,9 @@ SubcellArgs subcell_args(const nsk_ctx* c) {
 // Model II with FV sub-cells: indicator, the elements needing sub-cell means,
 // the means, the lifting, the DG right-hand side of the untroubled
 // elements, then the FV sub-cell update of the troubled ones.
-template <int DIM, int NP, int EPB>
+template <int DIM, int NP, int EPB, int FORM>
 int launch_stage_subcell(nsk_ctx* c, const double* Uin, double* Uout, double* dU, const StageArgs& st) {
-  using Tl = Tile<DIM, NP, EPB>;
+  using Tl = Tile<DIM, NP, EPB, FORM>;
   const BasisArgs b = basis_args(c);
   const MeshArgs m = mesh_args(c);
   const PhysArgs p = phys_args(c);
@@ -110,8 +110,8 @@ int launch_stage_subcell(nsk_ctx* c, const double* Uin, double* Uout, double* dU
   const unsigned E = (unsigned)c->E;
   hipEvent_t* ev = stage_events(c, st);
   if (ev) (void)hipEventRecord(ev[0], c->stream);
-  hipLaunchKernelGGL((lift_kernel<DIM, NP, EPB, double, double>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin,
-                     G, b, m, p);
+  hipLaunchKernelGGL((lift_kernel<DIM, NP, EPB, double, double, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream,
+                     Uin, G, b, m, p);
   if (ev) (void)hipEventRecord(ev[1], c->stream);
   constexpr int EPG = PerssonTile<DIM, NP>::EPG;
   hipLaunchKernelGGL((persson_kernel<DIM, NP>), dim3((E + EPG - 1) / EPG), dim3(kSubThreads), 0, c->stream, Uin, sa,
@@ -124,13 +124,13 @@ int launch_stage_subcell(nsk_ctx* c, const double* Uin, double* Uout, double* dU
   StageArgs sta = st;
   sta.skip = sa.flags;
   if (c->par.flux == 1) {
-    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, double, double, 1>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream,
-                       Uin, G, Uout, dU, b, m, p, sta);
+    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, double, double, 1, 0, FORM>), dim3(blocks), dim3(Tl::THREADS), 0,
+                       c->stream, Uin, G, Uout, dU, b, m, p, sta);
     hipLaunchKernelGGL((fv_kernel<DIM, NP, 1>), dim3(E), dim3(kSubThreads), 0, c->stream, Uin, G, Uout, dU, b, m, p,
                        sta, sa);
   } else {
-    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, double, double, 0>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream,
-                       Uin, G, Uout, dU, b, m, p, sta);
+    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, double, double, 0, 0, FORM>), dim3(blocks), dim3(Tl::THREADS), 0,
+                       c->stream, Uin, G, Uout, dU, b, m, p, sta);
     hipLaunchKernelGGL((fv_kernel<DIM, NP, 0>), dim3(E), dim3(kSubThreads), 0, c->stream, Uin, G, Uout, dU, b, m, p,
                        sta, sa);
   }
@@ -138,13 +138,13 @@ int launch_stage_subcell(nsk_ctx* c, const double* Uin, double* Uout, double* dU
   return hipGetLastError() == hipSuccess ? NSK_OK : NSK_EHIP;
 }
 
-template <int DIM, int NP, int EPB, typename R, typename GT>
+template <int DIM, int NP, int EPB, typename R, typename GT, int FORM = kLines>
 int launch_stage_e(nsk_ctx* c, const double* Uin, double* Uout, double* dU, const StageArgs& st) {
   if constexpr (std::is_same<R, double>::value) {
-    if (c->par.model == 1) return launch_stage_nsk<DIM, NP, EPB>(c, Uin, Uout, dU, st);
-    if (c->par.subcell == 1) return launch_stage_subcell<DIM, NP, EPB>(c, Uin, Uout, dU, st);
+    if (c->par.model == 1) return launch_stage_nsk<DIM, NP, EPB, FORM>(c, Uin, Uout, dU, st);
+    if (c->par.subcell == 1) return launch_stage_subcell<DIM, NP, EPB, FORM>(c, Uin, Uout, dU, st);
   }
-  using Tl = Tile<DIM, NP, EPB>;
+  using Tl = Tile<DIM, NP, EPB, FORM>;
   const BasisArgs b = basis_args(c);
   const MeshArgs m = mesh_args(c);
   const PhysArgs p = phys_args(c);
@@ -152,8 +152,8 @@ int launch_stage_e(nsk_ctx* c, const double* Uin, double* Uout, double* dU, cons
   const unsigned blocks = (unsigned)((c->E + EPB - 1) / EPB);
   hipEvent_t* ev = stage_events(c, st);
   if (ev) (void)hipEventRecord(ev[0], c->stream);
-  hipLaunchKernelGGL((lift_kernel<DIM, NP, EPB, R, GT>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b, m,
-                     p);
+  hipLaunchKernelGGL((lift_kernel<DIM, NP, EPB, R, GT, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G, b,
+                     m, p);
   if (ev) (void)hipEventRecord(ev[1], c->stream);
   StageArgs sta = st;
   if (c->par.closure == 1) {
@@ -169,17 +169,25 @@ int launch_stage_e(nsk_ctx* c, const double* Uin, double* Uout, double* dU, cons
   }
   if (ev) (void)hipEventRecord(ev[2], c->stream);
   if (c->par.flux == 1)
-    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, R, GT, 1>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G,
-                       Uout, dU, b, m, p, sta);
+    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, R, GT, 1, 0, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream,
+                       Uin, G, Uout, dU, b, m, p, sta);
   else
-    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, R, GT, 0>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream, Uin, G,
-                       Uout, dU, b, m, p, sta);
+    hipLaunchKernelGGL((rhs_kernel<DIM, NP, EPB, R, GT, 0, 0, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, c->stream,
+                       Uin, G, Uout, dU, b, m, p, sta);
   if (ev) (void)hipEventRecord(ev[3], c->stream);
   return hipGetLastError() == hipSuccess ? NSK_OK : NSK_EHIP;
 }
 
 template <int DIM, int NP, typename R, typename GT>
 int launch_stage_t(nsk_ctx* c, const double* Uin, double* Uout, double* dU, const StageArgs& st) {
+  if constexpr (Ends<DIM, NP>::built) {
+    if (Ends<DIM, NP>::pays(c))
+      return launch_stage_e<DIM, NP, Ends<DIM, NP>::EPB, R, GT, kEnds>(c, Uin, Uout, dU, st);
+  }
+  if constexpr (Staged<DIM, NP, R>::built) {
+    if (Staged<DIM, NP, R>::pays(c))
+      return launch_stage_e<DIM, NP, Epb<DIM, NP>::V0, R, GT, kStaged>(c, Uin, Uout, dU, st);
+  }
   if (c->tile == 1 && Epb<DIM, NP>::V1 != Epb<DIM, NP>::V0)
     return launch_stage_e<DIM, NP, Epb<DIM, NP>::V1, R, GT>(c, Uin, Uout, dU, st);
   return launch_stage_e<DIM, NP, Epb<DIM, NP>::V0, R, GT>(c, Uin, Uout, dU, st);
