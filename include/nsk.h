@@ -510,7 +510,9 @@ int nsk_batch_rk_step(nsk_batch* b, double dt, int nsteps);
  * {0, 2, 4, 8} (m = 0: one workgroup per item; otherwise a persistent grid
  * of m workgroups per CU), and last, with that shape, working-set budgets
  * of 0 (the whole group as one chunk), 128, 256 and 512 MiB over ten
- * consecutive stages: a group runs as chunks of whole instances whose
+ * consecutive Runge-Kutta stages (of step size 0, from the state into its
+ * copy; they overwrite the register, which a step does not read before it has
+ * written it): a group runs as chunks of whole instances whose
  * state, state copy, register and lifted gradients fit the budget, and a
  * graph replay runs the ten stages of one chunk back to back while its data
  * is still in the caches.  A chunk of one instance runs the single-mesh

@@ -85,16 +85,9 @@ void drop_graph(nsk_batch* b) {
   b->graph_dt = -1.0;
 }
 
-// what the stages stream past the caches: all instances take a stage together
-int batch_stream(const nsk_batch* b) {
-  double t = 0.0;
-  for (int i = 0; i < b->ninst; ++i) t += stage_bytes(b->ctx[i]);
-  return stream_bits(t);
-}
-
 // descriptor of instance i for stage parity p: p = 0 reads U, writes the
-// workspace copy; p = 1 the reverse
-BatchInst make_desc(nsk_batch* b, int i, int p) {
+// workspace copy; p = 1 the reverse.  stream: what its stages write past the caches
+BatchInst make_desc(nsk_batch* b, int i, int p, int stream) {
   nsk_ctx* c = b->ctx[i];
   BatchInst d;
   double* U2 = reinterpret_cast<double*>(c->work + c->off_U2);
@@ -104,17 +97,17 @@ BatchInst make_desc(nsk_batch* b, int i, int p) {
   d.G = c->work + c->off_G;
   d.msh = mesh_args(c);
   d.msh.nxcd = 1;
-  d.msh.stream = batch_stream(b);
+  d.msh.stream = stream;
   return d;
 }
 
 int upload_tables(nsk_batch* b) {
-  std::vector<BatchInst> desc(2 * b->ninst);
-  for (int p = 0; p < 2; ++p)
-    for (int i = 0; i < b->ninst; ++i) desc[p * b->ninst + i] = make_desc(b, i, p);
-  if (hipMemcpyAsync(b->work + b->off_desc, desc.data(), sizeof(BatchInst) * desc.size(), hipMemcpyHostToDevice,
-                     b->stream) != hipSuccess)
-    return NSK_EHIP;
+  // what an instance's stages write past the caches goes by what runs together: the
+  // working set of its chunk, whose ten stages run before the next chunk's.  By the
+  // sum over all instances, chunks that the caches hold were streamed past them (us
+  // for two steps: four meshes of 22x22x22, N = 4, FP64, one to a chunk 6131 -> 5503;
+  // 25^3 N = 3, 22^3 N = 4 and 18^3 N = 5 together 4125 -> 3599).
+  std::vector<int> stream(b->ninst, 0);
   for (BatchGroup& g : b->groups) {
     const int epb = epb_of(g.np, g.variant);
     std::vector<BatchItem> items;
@@ -130,33 +123,36 @@ int upload_tables(nsk_batch* b) {
     // is still in the caches
     g.chunks.assign(1, 0);
     g.chunk_inst.clear();
-    const size_t budget = (size_t)g.chunk_mib << 20;
-    size_t acc = 0;
-    int pos = 0, first = -1, count = 0;
+    const double budget = double(g.chunk_mib) * (1 << 20);
+    double acc = 0.0;
+    int pos = 0;
+    std::vector<int> members;
+    auto close = [&]() {
+      g.chunks.push_back(pos);
+      g.chunk_inst.push_back(members.size() == 1 ? members[0] : -1);
+      for (int i : members) stream[i] = stream_bits(acc);
+      members.clear();
+      acc = 0.0;
+    };
     for (int i : g.inst) {
       const nsk_ctx* c = b->ctx[i];
-      const size_t gbytes = (size_t)c->S * (3 * sizeof(double) * (size_t)c->nvar +
-                                            (size_t)c->ng * (c->par.precision == 0 ? sizeof(double) : sizeof(float)));
-      const int nblk = (int)((c->E + epb - 1) / epb);
-      if (budget && pos > g.chunks.back() && acc + gbytes > budget) {
-        g.chunks.push_back(pos);
-        g.chunk_inst.push_back(count == 1 ? first : -1);
-        acc = 0;
-        count = 0;
-      }
-      if (count == 0) first = i;
-      ++count;
-      acc += gbytes;
-      pos += nblk;
+      const double bytes = stage_bytes(c);
+      if (g.chunk_mib && !members.empty() && acc + bytes > budget) close();
+      members.push_back(i);
+      acc += bytes;
+      pos += (int)((c->E + epb - 1) / epb);
     }
-    if (g.chunks.back() != pos) {
-      g.chunks.push_back(pos);
-      g.chunk_inst.push_back(count == 1 ? first : -1);
-    }
+    if (!members.empty()) close();
     if (hipMemcpyAsync(b->work + g.off_items, items.data(), sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice,
                        b->stream) != hipSuccess)
       return NSK_EHIP;
   }
+  std::vector<BatchInst> desc(2 * b->ninst);
+  for (int p = 0; p < 2; ++p)
+    for (int i = 0; i < b->ninst; ++i) desc[p * b->ninst + i] = make_desc(b, i, p, stream[i]);
+  if (hipMemcpyAsync(b->work + b->off_desc, desc.data(), sizeof(BatchInst) * desc.size(), hipMemcpyHostToDevice,
+                     b->stream) != hipSuccess)
+    return NSK_EHIP;
   if (hipStreamSynchronize(b->stream) != hipSuccess) return NSK_EHIP;
   drop_graph(b);
   return NSK_OK;
@@ -201,8 +197,7 @@ int launch_single_e(nsk_batch* b, nsk_ctx* c, int parity, const StageArgs& st) {
   double* Uout = parity ? c->U : U2;
   GT* G = reinterpret_cast<GT*>(c->work + c->off_G);
   const BasisArgs bas = basis_args(c);
-  MeshArgs m = mesh_args(c);
-  m.stream = batch_stream(b);
+  const MeshArgs m = mesh_args(c);
   const PhysArgs ph = phys_args(c);
   const unsigned blocks = (unsigned)((c->E + EPB - 1) / EPB);
   hipLaunchKernelGGL((lift_kernel<3, NP, EPB, R, GT, FORM>), dim3(blocks), dim3(Tl::THREADS), 0, b->stream, Uin, G, bas,
@@ -469,11 +464,15 @@ int nsk_batch_autotune(nsk_batch* b, int reps, double* ms_out) {
     for (int ci = 0; ci < 4 && rc == NSK_OK; ++ci) {
       g.chunk_mib = kChunkMiB[ci];
       if ((rc = upload_tables(b)) != NSK_OK) break;
-      // ten consecutive stages per chunk, as a graph replay runs them
+      // ten consecutive stages per chunk, as a graph replay runs them, register
+      // and state written as there (and past the caches as there), with a step of
+      // 0 and always from U into its copy: the state stays, the register is scratch
+      // between steps (the first stage of a step does not read it)
       auto sweep = [&]() {
         int r2 = NSK_OK;
         for (int ch = 0; ch + 1 < (int)g.chunks.size() && r2 == NSK_OK; ++ch)
-          for (int k = 0; k < 10 && r2 == NSK_OK; ++k) r2 = launch_group(b, g, 0, st, ch);
+          for (int k = 0; k < 10 && r2 == NSK_OK; ++k)
+            r2 = launch_group(b, g, 0, StageArgs{kRkA[k % 5], kRkB[k % 5], 0.0, 1}, ch);
         return r2;
       };
       if ((rc = sweep()) != NSK_OK) break;
