@@ -435,8 +435,9 @@ size_t nsk_mlp_workspace_bytes(long long batch);
  * rounding points (BF16 parameters, BF16 activations of the first two hidden
  * layers; the backward pass takes that rounding as the identity).  Sample s
  * is row d_idx[s] of d_X[.][4] and d_Y[.][2] (d_idx may be NULL: row s).
- * d_grad receives NSK_MLP_NPARAM floats, d_loss (may be NULL) one float.  The
- * per-workgroup partial sums are added in a fixed order (deterministic).
+ * d_grad receives NSK_MLP_NPARAM floats, d_loss (may be NULL) one float.  Sums
+ * over samples are FP32 over tiles of 128 and FP64 over the tiles, in a fixed order
+ * (deterministic).
  * d_ws: nsk_mlp_workspace_bytes(n) bytes.  Asynchronous on hip_stream. */
 int nsk_mlp_loss_grad(const uint16_t* d_w_bf16, const float* d_X, const float* d_Y, const int* d_idx, long long n,
                       float tscale0, float tscale1, void* d_ws, float* d_grad, float* d_loss, void* hip_stream);

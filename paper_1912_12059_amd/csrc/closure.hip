@@ -52,11 +52,19 @@ mlp_forward_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, 
 // no sum crosses waves.
 //
 // All four 64x64 products of the backward pass multiply an FP32 value (dz) by
-// a BF16 one (a weight or an activation).  dz is split into three BF16 terms,
-// which hold its 24 bits exactly; the products are then exact and are added in
-// FP32 in the accumulators, as before.  That is three BF16 matrix products of
-// 16 steps where the FP32 ones would take eight of 2 (96 cycles against 512).
-// The gradient's error against 64 bits is unchanged (9.8e-6 of its norm, both).
+// a BF16 one (a weight or an activation).  dz is split into three BF16 terms of 8
+// bits, which hold its 24 exactly; the products are then exact and are added in
+// FP32 in the accumulators.  That is three BF16 matrix products of 16 steps where
+// the FP32 ones would take eight of 2 (96 cycles against 512).  An infinite dz is
+// in every term, so that its products are what they are in FP32.
+//
+// Sums over samples are FP32 within a tile, 8 matrix steps of 16 samples or 32
+// additions, and FP64 beyond it, over the tiles of a workgroup and over the
+// workgroups (the kernel with one thread a value added 32 samples in FP32 and the
+// rest in FP64).  FP32 over a workgroup's tiles loses what they add to a large sum: with
+// 32 tiles, the first with residuals of 1 and the others of 2^-22, 124 2^-24 of the
+// result.  The FP64 sums take 12 % where a workgroup walks (372 -> 422 us at 2^20
+// samples); up to 256 tiles each workgroup has one (WALK false) and there are none.
 //
 // Measured at a batch of 32768: 21 us, and 4.5 us for the sum over workgroups
 // (76 and 38 us with 1024 workgroups of 32 samples in vector arithmetic, whose
@@ -130,10 +138,36 @@ __device__ __forceinline__ void put_activation(const f32x16 (&z)[2], bf16x4 (&bo
     }
 }
 
+// d *= g'(z) from the bits of m.  True where the wave holds an infinite or NaN
+// value: there a product, as infinity times 0 is NaN and has to stay so.
+__device__ __forceinline__ bool mask_gradient(f32x16 (&d)[2], uint32_t m) {
+  float s = 0.f;
+#pragma unroll
+  for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s = fmaf(d[ib][r], 0.f, s);
+  const bool bad = __any(s != s);
+  if (bad) {
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) d[ib][r] *= float((m >> (ib * 16 + r)) & 1u);
+  } else {
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) d[ib][r] = (m >> (ib * 16 + r)) & 1u ? d[ib][r] : 0.f;
+  }
+  return bad;
+}
+
 // The three BF16 terms of dz, largest first, as operands and into
-// sDz[term][unit][sample].
+// sDz[term][unit][sample]: the upper half of its bits, then of what is left.
+// INF: values may be infinite; what is left of one is taken to be itself.
+template <bool INF>
 __device__ __forceinline__ void put_split(const f32x16 (&dz)[2], bf16x4 (&term)[3][8], uint16_t* sDz, int half,
                                           int sample) {
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
   for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
@@ -143,15 +177,27 @@ __device__ __forceinline__ void put_split(const f32x16 (&dz)[2], bf16x4 (&term)[
       for (int q = 0; q < 4; ++q) v[q] = dz[ib][4 * g + q];
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        const bf16x4 b = bf16_pack4(v[0], v[1], v[2], v[3]);
+        const auto up = [&](int q) {
+          return __builtin_amdgcn_perm(__float_as_uint(v[q + 1]), __float_as_uint(v[q]), 0x07060302u);
+        };
+        const bf16x4 b = __builtin_bit_cast(bf16x4, (u32x2_t){up(0), up(2)});
         term[p][4 * ib + g] = b;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           sDz[(p * kMlpHid + ib * 32 + 8 * g + 4 * half + q) * kSPad + sample] = uint16_t(b[q]);
-          v[q] -= bf16_to_f32(uint16_t(b[q]));
+          const float t = __uint_as_float(__float_as_uint(v[q]) & 0xFFFF0000u);
+          v[q] = INF && fabsf(t) == INFINITY ? t : v[q] - t;
         }
       }
     }
+}
+
+// register k of g
+__device__ __forceinline__ float acc_at(const f32x16& g, int k) {
+  float v = g[0];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) v = k == r ? g[r] : v;
+  return v;
 }
 
 // gw += the 32x32 block (ub, jb) of sum_s dz[u][s] h[j][s] over the tile, and
@@ -174,6 +220,8 @@ __device__ __forceinline__ void weight_gradient(f32x16& gw, f32x16& gb, bool bia
   }
 }
 
+// WALK: a workgroup may have more than one tile.
+template <bool WALK>
 __global__ void __launch_bounds__(kTrainThreads, 1)
 mlp_train_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, const float* __restrict__ Yt,
                  const int* __restrict__ idx, long long n, float inv_n, float tscale0, float tscale1,
@@ -223,15 +271,41 @@ mlp_train_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, co
     }
   }
   const int ub = wave >> 1, jb = wave & 1;
+  // sums of a tile, and FP64 ones of the tiles before it; every column of gB2 and
+  // gB3 is the same, a lane keeps register col % 16
   f32x16 gW2, gW3, gB2, gB3;
+  float gV[8], loss;  // W4 (2), b4, W1 (4), b1
+  double aW2[WALK ? 16 : 1], aW3[WALK ? 16 : 1], aB2 = 0.0, aB3 = 0.0, aV[8], aLoss = 0.0;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) gW2[r] = gW3[r] = gB2[r] = gB3[r] = 0.f;
-  float gW4[kMlpOut] = {0.f, 0.f}, gB4 = 0.f, gW1[kMlpIn] = {0.f, 0.f, 0.f, 0.f}, gB1 = 0.f, loss = 0.f;
+  for (int r = 0; WALK && r < 16; ++r) aW2[r] = aW3[r] = 0.0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) aV[k] = 0.0;
+  const auto clear = [&]() {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) gW2[r] = gW3[r] = gB2[r] = gB3[r] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) gV[k] = 0.f;
+    loss = 0.f;
+  };
+  clear();
   const int vu = t & 63, vq = t >> 6;  // unit and quarter of the samples in the vector sums
   __syncthreads();
 
   const long long tiles = (n + T - 1) / T;
-  for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+  for (long long tile = blockIdx.x; tile < (WALK ? tiles : blockIdx.x + 1); tile += gridDim.x) {
+    if (WALK && tile != blockIdx.x) {
+#pragma unroll
+      for (int r = 0; WALK && r < 16; ++r) {
+        aW2[r] += double(gW2[r]);
+        aW3[r] += double(gW3[r]);
+      }
+      aB2 += double(acc_at(gB2, col & 15));
+      aB3 += double(acc_at(gB3, col & 15));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) aV[k] += double(gV[k]);
+      aLoss += double(loss);
+      clear();
+    }
     const long long g = tile * T + smp;
     const long long src = g < n ? (idx ? (long long)idx[g] : g) : 0;
     const Row4 x = g < n ? reinterpret_cast<const Row4*>(X)[src] : Row4{0.f, 0.f, 0.f, 0.f};
@@ -289,11 +363,13 @@ mlp_train_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, co
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int u = ib * 32 + mfma_row(r, half);
-        const float dh = sP[kCW4 + u] * dy[0] + sP[kCW4 + Hd + u] * dy[1];
-        acc[ib][r] = (m3 >> (ib * 16 + r)) & 1u ? dh : 0.f;
+        acc[ib][r] = sP[kCW4 + u] * dy[0] + sP[kCW4 + Hd + u] * dy[1];
       }
     bf16x4 term[3][8];
-    put_split(acc, term, sDz, half, smp);
+    if (mask_gradient(acc, m3))
+      put_split<true>(acc, term, sDz, half, smp);
+    else
+      put_split<false>(acc, term, sDz, half, smp);
     // dz2 = (W3^T dz3) g'(z2), smallest terms first
 #pragma unroll
     for (int ib = 0; ib < 2; ++ib)
@@ -301,10 +377,7 @@ mlp_train_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, co
       for (int r = 0; r < 16; ++r) acc[ib][r] = 0.f;
 #pragma unroll
     for (int p = 2; p >= 0; --p) acc_product(acc, sWT + Hd * kWPad, term[p], half, col);
-#pragma unroll
-    for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[ib][r] = (m2 >> (ib * 16 + r)) & 1u ? acc[ib][r] : 0.f;
+    const bool bad = mask_gradient(acc, m2);
     __syncthreads();
     // layer 3 and output layer gradients
     weight_gradient(gW3, gB3, jb == 0, sDz, sH[1], ub, jb, half, col);
@@ -312,12 +385,15 @@ mlp_train_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, co
     for (int i = 0; i < T / 4; ++i) {
       const int s = vq * (T / 4) + i;
       const float h = sF[vu * kSPadF + s], d0 = sDy[0][s], d1 = sDy[1][s];
-      gW4[0] += d0 * h;
-      gW4[1] += d1 * h;
-      gB4 += vu == 0 ? d0 : d1;
+      gV[0] += d0 * h;
+      gV[1] += d1 * h;
+      gV[2] += vu == 0 ? d0 : d1;
     }
     __syncthreads();
-    put_split(acc, term, sDz, half, smp);
+    if (bad)
+      put_split<true>(acc, term, sDz, half, smp);
+    else
+      put_split<false>(acc, term, sDz, half, smp);
     // dz1 = (W2^T dz2) g'(z1)
 #pragma unroll
     for (int ib = 0; ib < 2; ++ib)
@@ -329,7 +405,7 @@ mlp_train_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, co
     for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        sF[(ib * 32 + mfma_row(r, half)) * kSPadF + smp] = (m1 >> (ib * 16 + r)) & 1u ? acc[ib][r] : 0.f;
+        sF[(ib * 32 + mfma_row(r, half)) * kSPadF + smp] = acc[ib][r] * float((m1 >> (ib * 16 + r)) & 1u);
     __syncthreads();
     // layer 2 and layer 1 gradients
     weight_gradient(gW2, gB2, jb == 0, sDz, sH[0], ub, jb, half, col);
@@ -338,31 +414,44 @@ mlp_train_kernel(const uint16_t* __restrict__ w, const float* __restrict__ X, co
       const int s = vq * (T / 4) + i;
       const float d = sF[vu * kSPadF + s];
       const float4 xs = sX[s];
-      gW1[0] += d * xs.x;
-      gW1[1] += d * xs.y;
-      gW1[2] += d * xs.z;
-      gW1[3] += d * xs.w;
-      gB1 += d;
+      gV[3] += d * xs.x;
+      gV[4] += d * xs.y;
+      gV[5] += d * xs.z;
+      gV[6] += d * xs.w;
+      gV[7] += d;
     }
     __syncthreads();  // the next tile overwrites the buffers
   }
 
+  float gb2 = acc_at(gB2, col & 15), gb3 = acc_at(gB3, col & 15);
+  if (WALK) {
+#pragma unroll
+    for (int r = 0; WALK && r < 16; ++r) {
+      gW2[r] = float(aW2[r] + double(gW2[r]));
+      gW3[r] = float(aW3[r] + double(gW3[r]));
+    }
+    gb2 = float(aB2 + double(gb2));
+    gb3 = float(aB3 + double(gb3));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) gV[k] = float(aV[k] + double(gV[k]));
+    loss = float(aLoss + double(loss));
+  }
   float* out = part + (long long)blockIdx.x * (kMlpParams + 1);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int u = ub * 32 + mfma_row(r, half);
     out[kOffW3 + u * Hd + jb * 32 + col] = gW3[r];
     out[kOffW2 + u * Hd + jb * 32 + col] = gW2[r];
-    if (jb == 0 && col == 0) {
-      out[kOffB3 + u] = gB3[r];
-      out[kOffB2 + u] = gB2[r];
-    }
+  }
+  if (jb == 0 && col < 16) {
+    const int u = ub * 32 + mfma_row(col, half);
+    out[kOffB3 + u] = gb3;
+    out[kOffB2 + u] = gb2;
   }
   // the quarters' vector sums and the waves' losses, added in order
   float* red = sF;  // [quarter][8][unit]
-  const float v[8] = {gW4[0], gW4[1], gB4, gW1[0], gW1[1], gW1[2], gW1[3], gB1};
 #pragma unroll
-  for (int k = 0; k < 8; ++k) red[(vq * 8 + k) * 64 + vu] = v[k];
+  for (int k = 0; k < 8; ++k) red[(vq * 8 + k) * 64 + vu] = gV[k];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
   if (lane == 0) sDy[0][wave] = loss;
@@ -676,7 +765,8 @@ int nsk_mlp_loss_grad(const uint16_t* d_w, const float* d_X, const float* d_Y, c
   const int grid = (int)std::min<long long>((n + kTrainSamples - 1) / kTrainSamples, kTrainGrid);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   float* part = static_cast<float*>(d_ws);
-  hipLaunchKernelGGL(mlp_train_kernel, dim3((unsigned)grid), dim3(kTrainThreads), 0, s, d_w, d_X, d_Y, d_idx, n,
+  const auto train = n > (long long)kTrainSamples * kTrainGrid ? mlp_train_kernel<true> : mlp_train_kernel<false>;
+  hipLaunchKernelGGL(train, dim3((unsigned)grid), dim3(kTrainThreads), 0, s, d_w, d_X, d_Y, d_idx, n,
                      float(1.0 / double(n)), tscale0, tscale1, part);
   hipLaunchKernelGGL(mlp_reduce_kernel, dim3((kMlpParams + 1 + kRedCols - 1) / kRedCols), dim3(kRedCols * kRedWaves), 0,
                      s, part, grid, d_grad, d_loss);
