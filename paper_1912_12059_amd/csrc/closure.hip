@@ -77,6 +77,11 @@ constexpr int kTrainGrid = 256;     // workgroups at most: one per CU
 constexpr int kSPad = kTrainSamples + 8;   // BF16 values per unit, rows 16-byte aligned and off the bank period
 constexpr int kSPadF = kTrainSamples + 1;  // FP32 values per unit
 
+// 16 bytes of parameters at any address a uint16_t may have
+struct __attribute__((packed, aligned(2))) ParamWord16 {
+  uint32_t x, y, z, w;
+};
+
 // a sample's features and targets (any address a float may have)
 struct __attribute__((packed, aligned(4))) Row4 {
   float x, y, z, w;

@@ -63,8 +63,6 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_floa
 // round to nearest even (the conversion lowers to v_cvt_pk_bf16_f32)
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
-__device__ __forceinline__ float bf16_round(float f) { return bf16_to_f32(f32_to_bf16(f)); }
-
 // ---- activation ---------------------------------------------------------------
 // ReLU, g(z) = max(z, 0), with derivative 1 for z > 0 and 0 otherwise.  On
 // the bit pattern of an IEEE value it is the signed-integer maximum with 0
@@ -72,8 +70,6 @@ __device__ __forceinline__ float bf16_round(float f) { return bf16_to_f32(f32_to
 // v_max_i32, without the quieting of signalling NaNs that fmaxf adds for
 // operands the compiler cannot prove canonical, such as MFMA results.
 __device__ __forceinline__ float act_f(float z) { return __int_as_float(max(__float_as_int(z), 0)); }
-
-__device__ __forceinline__ float act_df(float z) { return z > 0.f ? 1.f : 0.f; }
 
 // ---- element-local features ---------------------------------------------------
 template <int DIM, int NP>
@@ -297,21 +293,16 @@ __device__ __forceinline__ void mlp_wave(const float4* sX, const uint16_t* sW, c
   }
 }
 
-// 16 bytes of parameters at any address a uint16_t may have (inference wants
-// its parameters 16-byte aligned, training does not).
-struct __attribute__((packed, aligned(2))) ParamWord16 {
-  uint32_t x, y, z, w;
-};
-
 // Stage the parameters the network reads from LDS: W2, W3 as BF16 with
 // padded rows, and W1, b1, b2, b3, W4, b4 as FP32 in the compact block.
-// W2 and W3 move 8 values (16 bytes) per load.
+// W2 and W3 move 8 values (16 bytes) per load; w is 16-byte aligned and both
+// blocks start at multiples of 8 values.
 __device__ __forceinline__ void mlp_stage_params(const uint16_t* __restrict__ w, uint16_t* sW, float* sP) {
   static_assert(kOffW2 % 8 == 0 && kOffW3 % 8 == 0 && kMlpHid % 8 == 0 && kWPad % 4 == 0, "staging layout");
   constexpr int CH = kMlpHid / 8;  // 16-byte chunks per row
   for (int k = threadIdx.x; k < 2 * kMlpHid * CH; k += blockDim.x) {
     const int l = k / (kMlpHid * CH), r = (k / CH) % kMlpHid, cc = k % CH;
-    const ParamWord16 v = *reinterpret_cast<const ParamWord16*>(w + (l ? kOffW3 : kOffW2) + r * kMlpHid + 8 * cc);
+    const uint4 v = *reinterpret_cast<const uint4*>(w + (l ? kOffW3 : kOffW2) + r * kMlpHid + 8 * cc);
     uint2* dst = reinterpret_cast<uint2*>(sW + l * kMlpHid * kWPad + r * kWPad + 8 * cc);
     dst[0] = make_uint2(v.x, v.y);
     dst[1] = make_uint2(v.z, v.w);

@@ -1657,16 +1657,9 @@ rhs_kernel_batch1(const BatchInst* __restrict__ inst, const BatchItem* __restric
                                              I.msh, ph, st);
 }
 
-// The thread index handed to the block functions is made opaque in every
-// round: otherwise the compiler hoists the per-thread basis and index work
-// out of the loop and holds it in registers across items, which lowers
-// occupancy.
-__device__ __forceinline__ int opaque_tid() {
-  int t = threadIdx.x;
-  asm volatile("" : "+v"(t));
-  return t;
-}
-
+// The thread index handed to the block functions is opaque in every round:
+// otherwise the compiler hoists the per-thread basis and index work out of the loop
+// and holds it in registers across items, which lowers occupancy.
 template <int DIM, int NP, int EPB, typename R, typename GT, int FORM>
 __global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
 lift_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restrict__ items, int nitems,
@@ -1677,7 +1670,8 @@ lift_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restric
     if (it < nitems) {
       const BatchItem w = items[it];
       const BatchInst& I = inst[w.inst];
-      lift_block<DIM, NP, EPB, R, GT, 0, FORM>(w.L, opaque_tid(), I.U, reinterpret_cast<GT*>(I.G), bas, I.msh, ph);
+      lift_block<DIM, NP, EPB, R, GT, 0, FORM>(w.L, opaque(threadIdx.x), I.U, reinterpret_cast<GT*>(I.G), bas, I.msh,
+                                               ph);
     }
     __syncthreads();  // LDS is reused by the next item
   }
@@ -1693,8 +1687,8 @@ rhs_kernel_batch(const BatchInst* __restrict__ inst, const BatchItem* __restrict
     if (it < nitems) {
       const BatchItem w = items[it];
       const BatchInst& I = inst[w.inst];
-      rhs_block<DIM, NP, EPB, R, GT, 0, 0, FORM>(w.L, opaque_tid(), I.U, reinterpret_cast<const GT*>(I.G), I.Uout,
-                                                 I.dU, bas, I.msh, ph, st);
+      rhs_block<DIM, NP, EPB, R, GT, 0, 0, FORM>(w.L, opaque(threadIdx.x), I.U, reinterpret_cast<const GT*>(I.G),
+                                                 I.Uout, I.dU, bas, I.msh, ph, st);
     }
     __syncthreads();
   }
