@@ -1032,8 +1032,10 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   // (147 M lines of 128 bytes at 74 in flight a CU on average and 574 cycles, 96x48x48
   // elements, N = 4: 2.02 -> 1.96 ms).  They are loaded again where the registers
   // matter more: with staged neighbours (1.80 against 1.74 ms there in mixed
-  // precision), and with HLLC at N = 1 (384 against 373 us a stage, 120x60x60).
-  constexpr bool AGAIN = STAGE || (NP == 2 && FLUX == 1);
+  // precision), and with HLLC in FP64 at N = 1 in 3D (us for two steps, kept / again:
+  // 46x23x23 519 / 511, 121x60x60 3764 / 3709, 182x91x91 12581 / 12335; in mixed
+  // precision 10227 / 10399 there, in 2D 2394 / 2472 at 1414x707).
+  constexpr bool AGAIN = STAGE || (DIM == 3 && NP == 2 && FLUX == 1 && !MIXED);
   // With two lanes a line in 2D every load of the kernel is issued before the first
   // is waited for, unless that takes more registers than three waves a SIMD have
   // (N = 6 in FP64: 182; 3D: 204) or a fourth wave (MODEL 1: N = 4, 141x71, a stage
