@@ -228,14 +228,19 @@ int nsk_rk_step(nsk_ctx* ctx, double dt, int nsteps);
 int nsk_diagnostics(nsk_ctx* ctx, nsk_diag* host_out);
 
 /* Launch shape (performance only; results are bitwise identical for every
- * choice).  variant 0: as many elements per workgroup as fit about 256
- * threads within 40 KB of LDS; variant 1: half as many.  order selects the
+ * choice).  variant 0: as many elements per workgroup as have their lines of
+ * one direction in one wave and their node pairs in the waves of all (1D: 256
+ * nodes); variant 1: half as many in 1D and up to degree 2, the same from
+ * degree 3 in 2D and 3D.  order selects the
  * element work order: 0 natural order in the hardware's round-robin over
  * XCDs; 1 natural order cut into one contiguous range per XCD; 2..5 x-y
  * tiles of 4, 6, 8, 12 elements marched along z in 3D (x-strips of 16, 24,
  * 32, 48 elements marched along y in 2D), one contiguous range per XCD.
- * With a bound context a new order is uploaded at once (waits for the
- * stream).  Defaults: variant 0, order 4 in 3D, order 0 otherwise. */
+ * Small launches from degree 4 in 2D and at degree 4 in 3D take fewer elements
+ * per workgroup whatever the variant.  With a bound context a new order is
+ * uploaded at once (waits for the stream).  Defaults: variant 0; order 5 in 3D
+ * (4 from degree 3 where two states, register and gradients take at most
+ * 288 MB), 1 in 2D, 0 in 1D. */
 int nsk_set_tile(nsk_ctx* ctx, int variant, int order);
 
 /* Autotuner over the launch shapes of nsk_set_tile: times `reps`
@@ -321,8 +326,11 @@ size_t nsk_implicit_workspace_bytes(const nsk_ctx* ctx, int gmres_m);
 
 /* Advances the bound state by nsteps ESDIRK4(6) steps of size dt.  d_iwork:
  * caller-owned device memory of nsk_implicit_workspace_bytes(ctx,
- * opts->gmres_m) bytes, 256-byte aligned.  Synchronises the stream after
- * every Arnoldi step (the host needs the dot products).  Returns
+ * opts->gmres_m) bytes, 256-byte aligned.  The host waits for an event after
+ * every Arnoldi step (it needs the dot products, which a kernel writes to
+ * pinned host memory) and for the stream at the end: not for use while the
+ * stream is captured.  The first call of a context allocates those 544 bytes of
+ * pinned memory and the event; nsk_destroy frees them.  Returns
  * NSK_ENOCONV, with the state left at the last completed step, when a stage
  * misses newton_tol after newton_max corrections; NSK_EUNSUPPORTED for mixed
  * precision, closure or sub-cell contexts; NSK_EINVAL for invalid options or precond 1

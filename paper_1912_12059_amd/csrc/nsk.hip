@@ -606,11 +606,16 @@ int nsk_create(const nsk_mesh* mesh, const nsk_params* params, nsk_ctx** out) {
     off = align256(off + sizeof(double) * (size_t)(c->E + 1 + kMaxReduceBlocks));
   }
   c->ws_bytes = off;
-  // default launch shape: in 3D tiles of 12 elements' edge (3.06 ms a stage at
-  // 96x48x48, N = 4, FP64, 3.19 with edge 8 and 3.31 in natural order), in 2D
-  // the natural order in one contiguous range per XCD (24.4 us a stage at 96x96,
-  // N = 4, 27.8 in hardware round-robin)
-  c->order = c->dim == 3 ? 5 : (c->dim == 2 ? 1 : 0);
+  // default launch shape.  In 3D tiles of 12 elements' edge where the stages'
+  // working set is larger than the last-level cache, and below degree 3; of 8 where
+  // it fits.  us a step, edge 8 / 12: N = 4 32x16x16 FP64 101.5 / 107.0, 21x21x21 113.9 /
+  // 117.1, 73x36x36 1324 / 1286, 47x47x47 1455 / 1396; N = 5 26x13x13 mixed 89.0 / 96.1,
+  // 61x30x30 1426 / 1415; N = 3 40x20x20 mixed 70.9 / 72.1, 91x45x45 1108 / 1092; N = 2
+  // 53x26x26 88.9 / 87.6, 121x61x61 1411 / 1394; N = 1 51x51x51 88.3 / 86.8, 182x91x91
+  // 1228 / 1187.  In 2D the natural order in one contiguous range per XCD, within 1 %
+  // of the best at degrees 1 to 6 and 2e4 to 2e6 nodes (N = 4, 127x127: 34.7 us, 40.9 in
+  // hardware round-robin).
+  c->order = c->dim == 3 ? (c->N > 2 && stage_bytes(c) <= kStreamStateBytes ? 4 : 5) : (c->dim == 2 ? 1 : 0);
   *out = c;
   return NSK_OK;
 }
