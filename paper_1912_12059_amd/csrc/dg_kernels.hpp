@@ -1010,6 +1010,14 @@ __device__ __forceinline__ void face_flux(const R* uL, const R* uR, const R* vLR
 
 constexpr int kLineGroup = 3;
 
+// In 3D at degree 4 in mixed precision the right-hand side has four waves per SIMD,
+// five workgroups a CU instead of four: its registers are 131 with the own values
+// kept, 99 (two lanes a line) and 103 without.  It counts where a launch has one to two
+// rounds of workgroups (us for four steps, three waves / four: two lanes a line,
+// 16x9x8 517 / 482; a lane a line, 14x14x14 821 / 796, 32x16x16 both 1674).
+template <int DIM, int NP, typename R>
+constexpr bool kFourWaves = DIM == 3 && NP == 5 && sizeof(R) == 4;
+
 template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX, int MODEL, int FORM>
 __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __restrict__ U, const GT* __restrict__ G,
                                           double* __restrict__ Uout, double* __restrict__ dU, const BasisArgs& bas,
@@ -1034,8 +1042,9 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   // matter more: with staged neighbours (1.80 against 1.74 ms there in mixed
   // precision), and with HLLC in FP64 at N = 1 in 3D (us for two steps, kept / again:
   // 46x23x23 519 / 511, 121x60x60 3764 / 3709, 182x91x91 12581 / 12335; in mixed
-  // precision 10227 / 10399 there, in 2D 2394 / 2472 at 1414x707).
-  constexpr bool AGAIN = STAGE || (DIM == 3 && NP == 2 && FLUX == 1 && !MIXED);
+  // precision 10227 / 10399 there, in 2D 2394 / 2472 at 1414x707), and where it makes
+  // room for a fourth wave (kFourWaves).
+  constexpr bool AGAIN = STAGE || kFourWaves<DIM, NP, R> || (DIM == 3 && NP == 2 && FLUX == 1 && !MIXED);
   // With two lanes a line in 2D every load of the kernel is issued before the first
   // is waited for, unless that takes more registers than three waves a SIMD have
   // (N = 6 in FP64: 182; 3D: 204) or a fourth wave (MODEL 1: N = 4, 141x71, a stage
@@ -1571,9 +1580,11 @@ lift_kernel(const double* __restrict__ U, GT* __restrict__ G, BasisArgs bas, Mes
 // 96x48x48 elements); 2 waves lose (2.41 against 2.14 ms; degree 5, 48x24x24, a
 // stage: 0.86 against 0.73 ms).
 constexpr int kRhsWaves = 3;
+template <int DIM, int NP, typename R, int FORM>
+constexpr int kRhsWavesOf = kFourWaves<DIM, NP, R> && FORM != kStaged ? 4 : kRhsWaves;
 template <int DIM, int NP, int EPB, typename R, typename GT, int FLUX = 0, int MODEL = 0, int FORM = kLines>
 __global__ void __launch_bounds__((Tile<DIM, NP, EPB, FORM>::THREADS))
-    __attribute__((amdgpu_waves_per_eu(kRhsWaves)))
+    __attribute__((amdgpu_waves_per_eu((kRhsWavesOf<DIM, NP, R, FORM>))))
 rhs_kernel(const double* __restrict__ U, const GT* __restrict__ G, double* __restrict__ Uout,
            double* __restrict__ dU, BasisArgs bas, MeshArgs msh, PhysArgs ph, StageArgs st) {
   rhs_block<DIM, NP, EPB, R, GT, FLUX, MODEL, FORM>(remap_block(blockIdx.x, gridDim.x, msh.nxcd), threadIdx.x, U, G,

@@ -395,8 +395,8 @@ void subcell_matrices(const Basis1D& b, double M[kMaxNP][kMaxNP], double Minv[kM
 //             258x129 783 / 725, mixed 657 / 688
 //   2D N = 6  14x7 341 / 242, mixed 277 / 238; 156x78 1212 / 960, 938 / 849; 350x175
 //             2186 / 2235
-//   3D N = 4  7x3x3 334 / 255, mixed 354 / 247; 16x8x8 524 / 488, 471 / 426; 19x9x9
-//             676 / 705, mixed 558 / 624
+//   3D N = 4  7x3x3 334 / 255, mixed 354 / 253; 16x8x8 524 / 488, 471 / 426; 17x8x8
+//             602 / 580, mixed 506 / 479; 13x10x10 mixed 520 / 541; 19x9x9 676 / 705
 // In 2D at degree 4, and in mixed precision, the other form's fewer workgroups are
 // faster where they are one a CU and this form's are more: 59x29 N = 4 259 / 272,
 // mixed 242 / 258; 49x25 N = 6 mixed 286 / 290.
@@ -405,7 +405,7 @@ struct Ends {
   using Sh = Shape<DIM, NP>;
   static constexpr bool built = DIM > 1 && NP > 4 && 2 * Sh::NF <= 64;
   static constexpr int EPB = built ? 64 / (2 * Sh::NF) : 1;
-  static constexpr int most = NP == 5 ? 1024 : NP == 6 ? 4096 : 6144;
+  static constexpr int most = NP == 5 ? (DIM == 3 ? 1280 : 1024) : NP == 6 ? 4096 : 6144;
   static bool pays(const nsk_ctx* c) {
     constexpr int cus = 256;
     const long long mine = (c->E + EPB - 1) / EPB, other = (c->E + Epb<DIM, NP>::V0 - 1) / Epb<DIM, NP>::V0;
