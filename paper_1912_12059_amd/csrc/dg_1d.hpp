@@ -4,7 +4,8 @@
 // than one line's sums to form in turn.  (One lane per line, the form for 2D and
 // 3D, took 10.3 us a stage against 8.1 here at N = 5 on 900 elements, 8.0 against
 // 4.0 where the whole mesh is one workgroup.)  The operations on a value and their
-// order are those of the line kernels.
+// order are one in all 1D kernels, so that they give the same bits; unlike the line
+// kernels in FP64, which start a line from its faces' terms, these add them last.
 #pragma once
 
 namespace nsk {

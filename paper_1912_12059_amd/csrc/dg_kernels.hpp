@@ -263,15 +263,18 @@ __device__ __forceinline__ void block_max_store(double v, double* red, double* o
 // neighbours beside them.  In 3D three waves serve two elements at N = 4.
 // What bounds the 3D kernels at N = 4 now is the neighbours: without their loads
 // the right-hand side runs at the rate of its streams (1.42 ms for 6.6 GB).  It is
-// the L1's line requests that count (its wait for pending lines is 45 % of the
-// time): more waves a SIMD, or half as many load instructions for the same lines,
-// change nothing.
+// the L1's line requests that count: in the FP64 right-hand side at 96x48x48 elements
+// 133 M lines of 128 bytes a launch at 69 in flight a CU and 560 cycles each, 44 % of
+// the time stalled on pending lines; more waves a SIMD, or half as many load
+// instructions for the same lines, change nothing.
 //
-// Measured, ms a launch, one direction after the other / this form:
-//   3D N = 4, 96x48x48, FP64    lift 1.19 / 1.05   rhs 2.55 / 1.90
-//   3D N = 4, 96x48x48, mixed   lift 0.85 / 0.77   rhs 1.82 / 1.66
+// Measured, ms a launch, one direction after the other / this form with the fewer
+// registers and the streamed stores of below (without those two the FP64 right-hand
+// side took 2.04 and the lifting 1.11 ms, the mixed right-hand side 1.71):
+//   3D N = 4, 96x48x48, FP64    lift 1.19 / 1.04   rhs 2.55 / 1.89
+//   3D N = 4, 96x48x48, mixed   lift 0.85 / 0.76   rhs 1.82 / 1.66
 //   a stage: 3D N = 2, 96x48x48, FP64 1.17 / 0.70; N = 5, 48x24x24, mixed 0.83 / 0.57;
-//   2D N = 4, 96x96, FP64 0.0376 / 0.0244
+//   2D N = 4, 96x96, FP64 0.0376 / 0.0245
 // -------------------------------------------------------------------------
 // LDS position of node n of an element: even for even n, so that a pair of
 // values is one 16-byte access; the planes of lines of 2 or 4 nodes are padded
@@ -451,8 +454,9 @@ __device__ __forceinline__ LineRole line_role(const MeshArgs& m, int L, int sub,
 // pair a lane; staging whole neighbours through LDS for that (kStaged, into rows that
 // the own values take afterwards) needs one more barrier and twice the LDS
 // traffic.  It wins where the lines are long, LDS values are four bytes and the mesh
-// is large (Staged in host_common.hpp); it loses at N = 3 (0.79 ms both), N = 2
-// (0.63 against 0.60) and in FP64 (N = 4 1.03 against 0.95, N = 2 0.83 against 0.70).
+// is large (Staged in host_common.hpp); it gains nothing at N = 3 (0.79 ms both) and
+// loses at N = 2 (0.63 against 0.60) and in FP64 (N = 4 1.03 against 0.95, N = 2 0.83
+// against 0.70).
 
 // Places of a wave's neighbour pairs, round by round: the pair p and its
 // position at in LDS (-1: none), and the two neighbours.
@@ -1037,9 +1041,8 @@ __device__ __forceinline__ void rhs_block_lines(int L, int tid, const double* __
   constexpr bool ENDS = FORM == kEnds, STAGE = FORM == kStaged;
   // A pair's own values stay in registers to the end: 8 of the 81 components that
   // an element asks the L1 for, whose outstanding misses bound this kernel in 3D
-  // (147 M lines of 128 bytes at 74 in flight a CU on average and 574 cycles, 96x48x48
-  // elements, N = 4: 2.02 -> 1.96 ms).  They are loaded again where the registers
-  // matter more: with staged neighbours (1.80 against 1.74 ms there in mixed
+  // (96x48x48 elements, N = 4: 2.02 -> 1.96 ms).  They are loaded again where the
+  // registers matter more: with staged neighbours (1.80 against 1.74 ms there in mixed
   // precision), and with HLLC in FP64 at N = 1 in 3D (us for two steps, kept / again:
   // 46x23x23 519 / 511, 121x60x60 3764 / 3709, 182x91x91 12581 / 12335; in mixed
   // precision 10227 / 10399 there, in 2D 2394 / 2472 at 1414x707), and where it makes
@@ -1576,9 +1579,9 @@ lift_kernel(const double* __restrict__ U, GT* __restrict__ G, BasisArgs bas, Mes
 // The right-hand-side kernels are held to 3 waves per SIMD (168 VGPRs), where
 // they need no scratch: each spilled register of a thread is written to memory
 // (the degree 4 HLLC kernel with 38 spills: 10 % of a stage).  4 waves, with the LDS
-// for a fifth workgroup, gain nothing (2.02 ms both, degree 4 in 3D FP64,
-// 96x48x48 elements); 2 waves lose (2.41 against 2.14 ms; degree 5, 48x24x24, a
-// stage: 0.86 against 0.73 ms).
+// for a fifth workgroup, gained nothing (2.02 ms both, degree 4 in 3D FP64,
+// 96x48x48 elements, before stores were streamed); 2 waves lose (2.41 against 2.14
+// ms then; degree 5, 48x24x24, a stage: 0.86 against 0.73 ms).
 constexpr int kRhsWaves = 3;
 template <int DIM, int NP, typename R, int FORM>
 constexpr int kRhsWavesOf = kFourWaves<DIM, NP, R> && FORM != kStaged ? 4 : kRhsWaves;
