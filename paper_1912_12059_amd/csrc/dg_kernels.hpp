@@ -983,7 +983,16 @@ __device__ __forceinline__ void face_flux(const R* uL, const R* uR, const R* vLR
     // flux with the velocity of the upwind side of the contact
     // S* = F_hll[rho] / rho_hll; HLL dissipation alone on c
     const R vnL = uL[1 + d] * irL, vnR = uR[1 + d] * irR;
-    const R SL = fmin(vnL - aL, vnR - aR), SR = fmax(vnL + aL, vnR + aR);
+    // How the speeds are rounded is written out, SL from unrounded products and SR from
+    // rounded ones: chosen by the compiler it changes with the code around it, and a
+    // small v beside a large a then rounds differently in FP32 at one face in a
+    // thousand (mixed precision, seven steps, 3D N = 5: 2e-8 of the state).
+    const R SL = fmin(fma(uL[1 + d], irL, -aL), fma(uR[1 + d], irR, -aR));
+    R SR;
+    {
+#pragma clang fp contract(off)
+      SR = fmax(vnL + aL, vnR + aR);
+    }
     // all three cases by selection, a component at a time: branches keep more
     // alive than 168 registers hold at N = 4
     const bool l = SL >= R(0), r = SR <= R(0);
